@@ -342,13 +342,6 @@ __global__ __launch_bounds__(64 * W, NT <= 2 ? 2 : 1) void attn_tree_bf16_kernel
 // accumulators.  Probabilities stay below 2^8 in between; the shared maximum
 // is the same in every lane of a query vector, so the products stay exact.
 // Chunks entirely at or below every row of a wave skip the causal mask.
-// Two fp32 -> bf16 (round to nearest even) in one v_cvt_pk_bf16_f32.
-__device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
-  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-  typedef float f32x2_t __attribute__((ext_vector_type(2)));
-  const f32x2_t v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-}
 constexpr int kPrefillStagedPages = 1024;  // page ids kept in LDS (16384 keys)
 constexpr float kPrefillRescaleLog2 = 8.f;
 

@@ -88,7 +88,9 @@ size_t gemm_splitk_bytes(int R_max, int Nw_max);
 
 // Profiler name of the kernel launch_gemm uses for (dtype, R, N, K, epi) with
 // a split-K workspace of splitk_bytes, or launch_gemm_fused when fused.
+// normed, deferred: the launch is given a GemmNorm to apply (kEpiAddF32), or
+// one with defer set (kEpiStoreF32), and no row map.
 const char* gemm_kernel_name(int dtype, int R, int N, int K, int epi, bool fused = false,
-                             size_t splitk_bytes = 0);
+                             size_t splitk_bytes = 0, bool normed = false, bool deferred = false);
 
 }  // namespace spec

@@ -21,11 +21,14 @@
 //    the gate tile and its up tile); its waves split K and reduce through LDS
 //    in a fixed order (deterministic, no atomics).  M is padded to 16 per
 //    tile; MFMA throughput is ~10x what the weight stream needs.
-//  * mfma2 (R > 64, and the LM head / large projections above 8 / 40 rows):
-//    (32 MTW) x 256 workgroup tiles, one workgroup per CU, accumulators in
-//    AGPRs, X and W brought into LDS by direct-to-LDS loads four k-steps
-//    ahead, XCD-aware tile order, split-K with a fixed-order reduction when
-//    the grid is small.
+//  * mfma4 (R > 128, whole W tiles, K % 256 == 0): resident workgroups that
+//    walk tiles of 64 x 128 to 256 x 256, W straight into registers, X through
+//    LDS, the next tile's operands fetched during the last k-steps of a tile;
+//    split-K with a fixed-order reduction when the grid is small.
+//  * mfma3 (up to 128 rows, and the 4096-wide residual adds of the serving
+//    verify): the same operand paths, one tile per workgroup.
+//  * mfma2 (other shapes above 40 rows, the LM heads above 12): both operands
+//    through LDS by direct-to-LDS loads four k-steps ahead.
 //  * fp32 (the fp32 configuration): a plain LDS-tiled FMA kernel on row-major
 //    weights; no reduced-precision arithmetic.
 
@@ -975,6 +978,294 @@ __global__ __launch_bounds__(256, 1) void gemm_mfma3_bf16(const bf16_t* __restri
   }
 }
 
+// ---------------------------------------------------------------------------
+// MFMA bf16 for hundreds to thousands of rows (prefill chunks, the serving
+// verify): workgroup tile 16 MB rows x 64 NB W rows, 4 waves side by side
+// along W, W straight into registers and X through LDS as in gemm_mfma3_bf16,
+// and three differences that its counters asked for (8192-row gate/up: MFMA
+// pipe busy 57% of the time, the rest issue slots and per-tile start-up):
+//  * One MFMA per asm statement with nothing between two of them but one
+//    other instruction (a fragment read, one load, scalar address work), so
+//    that everything issues in the 16 cycles an MFMA occupies the pipe.  A
+//    wait state per four MFMAs and bunched loads cost 20% of the loop.
+//  * A fragment of X for the next k-step is read into the registers of the
+//    one whose last MFMA has just been issued: one register buffer instead of
+//    two, which makes room for 256 accumulators (MB 16), so that a 256 x 256
+//    tile reads 1 byte from LDS or L2 per 128 flops.
+//  * Workgroups stay resident and walk a list of tiles: the loads of the last
+//    k-steps of a tile already fetch the first ones of the next, so only the
+//    first tile pays the memory latency of a start, and the epilogue runs
+//    while the next tile's operands arrive.
+// Tiles are numbered in groups of kM4Group row tiles x all W tiles, and each
+// XCD walks a contiguous run of numbers, so that the tiles it works on at a
+// time share X and W panels in its L2.
+// Measured (median, weights rotated past the caches): 8192-row gate/up 1650 ->
+// 1340 us (1.43 PFLOP/s; the clock falls to 1.85 GHz under this load), 4096-row
+// QKV 242 -> 176, O 172 -> 117, down 455 -> 360 us.  32 x 32 MFMAs had 5% fewer
+// stall cycles and were 6% slower (more power per flop, lower clock); k-steps
+// started at different places per W tile were 3% slower.
+constexpr int kM4DW = 4, kM4DX = 8, kM4Group = 4;
+
+struct M4Tiles {
+  int MT, NT, S, k_len;  // row tiles, W tiles, K splits and their length
+};
+
+// The compiler does not know that this is an MFMA: nothing may write an
+// operand in the two wait states before it, nor read the accumulator until 18
+// wait states after it (a CPU test checks the first on the compiled kernel).
+__device__ __forceinline__ void mfma_acc_bare(f32x4& acc, const u32x4& a, const u32x4& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+
+template <int EPI, int MB, int NB, int OCC>
+__global__ __launch_bounds__(256, OCC) void gemm_mfma4_bf16(const bf16_t* __restrict__ X,
+                                                            const bf16_t* __restrict__ W, void* __restrict__ Y,
+                                                            float* __restrict__ part, int R, int N, int K,
+                                                            const M4Tiles tl, const int32_t* __restrict__ row_map) {
+  constexpr bool SW = (EPI == kEpiSwiGLU);
+  constexpr int DW = kM4DW, DX = kM4DX;
+  constexpr int TM = 16 * MB;
+  constexpr int NTG = 4 * NB;        // 16-feature W tiles per workgroup
+  constexpr int LX = MB / 4;         // X loads per wave per k-step
+  constexpr int XU = TM * 4;         // 16-byte units of X per stage
+  constexpr int PER = NB + LX;       // loads per wave per k-step
+  constexpr int NM = MB * NB;        // MFMAs per wave per k-step
+  constexpr int AW = DW - 1, AX = DX - 1;  // how many k-steps ahead W and X are loaded
+  // MFMAs between loads: a whole number of fragments where there are enough
+  constexpr int GAP = NM / PER >= NB ? (NM / PER) / NB * NB : NM / PER;
+  static_assert(MB % 4 == 0 && NB >= 2 && (!SW || NB % 2 == 0) && DX % DW == 0, "shape");
+  static_assert(GAP > 0 && GAP * (PER - 1) + 1 < NM, "every load has its place");
+  __shared__ u32x4 sx[DX * XU];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform: LDS targets in SGPRs
+  const int g = lane >> 4, l16 = lane & 15;
+
+  // this workgroup's tiles: workgroup s of the XCD's wx takes ids c0 + s,
+  // c0 + s + wx, ... of the XCD's run [c0, c1)
+  const int total = tl.MT * tl.NT * tl.S;
+  const int nwg = gridDim.x, xcd = blockIdx.x & 7;
+  const int wx = (nwg - xcd + 7) >> 3, before = (nwg >> 3) * xcd + min(xcd, nwg & 7);
+  const int c1 = static_cast<int>(static_cast<long long>(total) * (before + wx) / nwg);
+  int tix = static_cast<int>(static_cast<long long>(total) * before / nwg) + (blockIdx.x >> 3);
+  if (tix >= c1) return;
+  struct Tile {
+    int mt, nt, sp;
+  };
+  auto tile_of = [&](int id) {
+    Tile t;
+    const int per_split = tl.MT * tl.NT, gsz = kM4Group * tl.NT;
+    t.sp = id / per_split;
+    const int r = id - t.sp * per_split;
+    const int grp = r / gsz, gi = r - grp * gsz;
+    const int gm = min(kM4Group, tl.MT - grp * kM4Group);
+    t.nt = gi / gm;
+    t.mt = grp * kM4Group + gi - t.nt * gm;
+    return t;
+  };
+
+  // X load q of this wave: row group wave * LX + q (16 rows x 64 bytes), with
+  // gemm_mfma3_bf16's chunk swizzle; rows past R clamped (never written back).
+  // W fragment j: memory row tile * 16 + 4 ((k / 32) % 4) + g at chunk l16 of
+  // block k / 128; tiles past N clamped to the last one (N % 16 == 0).
+  uint32_t xo[LX], wo[NB];
+  auto set_x = [&](int mt) {
+#pragma unroll
+    for (int q = 0; q < LX; ++q)
+      xo[q] = (static_cast<uint32_t>(min(mt * TM + (wave * LX + q) * 16 + (lane >> 2), R - 1)) * K +
+               ((lane & 3) ^ (lane >> 4)) * 8) * 2;
+  };
+  auto set_w = [&](int nt) {
+    const int f = nt * (SW ? NTG / 2 : NTG);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int tile = min(SW ? f + wave * (NB / 2) + j % (NB / 2) : f + wave * NB + j, N / 16 - 1);
+      wo[j] = ((SW && j >= NB / 2) ? static_cast<uint32_t>(N) * K * 2u : 0u) +
+              (static_cast<uint32_t>(tile * 16 + g) * K + l16 * 8) * 2;
+    }
+  };
+  auto w_base = [&](int k) {
+    return reinterpret_cast<const char*>(W) +
+           static_cast<size_t>(static_cast<uint32_t>((k & 3) * 8) * static_cast<uint32_t>(K) + (k >> 2) * 256);
+  };
+  auto x_base = [&](int k) { return reinterpret_cast<const char*>(X) + k * 64; };
+  auto x_load = [&](int q, int stage, const char* base) {
+    load_lds16(base, xo[q], lds_addr(&sx[0]) + stage * (XU * 16) + (wave * LX + q) * 1024);
+  };
+  // A fragments: lane (l16, g) at unit l16 * 4 + (g ^ l16 / 4) of a row
+  // group; the stages past the 64 KB an LDS offset reaches have their own base
+  typedef __attribute__((address_space(3))) const u32x4* lds_units;
+  constexpr int LOW = 65536 / (XU * 16) < DX ? 65536 / (XU * 16) : DX;
+  const lds_units frag = (lds_units)&sx[l16 * 4 + (g ^ (l16 >> 2))];
+  lds_units frag_hi = frag + (LOW < DX ? LOW * XU : 0);
+  if (LOW < DX) asm("" : "+v"(frag_hi));
+
+  u32x4 wr[DW][NB];
+  u32x4 fa[MB];
+  f32x4 acc[MB][NB];
+  Tile cur = tile_of(tix);
+  set_x(cur.mt);
+  set_w(cur.nt);
+  int kx = cur.sp * (tl.k_len / 32), kw = kx;  // next k-step of X and of W to load
+#pragma unroll
+  for (int p = 0; p < AW; ++p, ++kw)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) load_reg16(wr[p][j], w_base(kw), wo[j]);
+#pragma unroll
+  for (int p = 0; p < AX; ++p, ++kx)
+#pragma unroll
+    for (int q = 0; q < LX; ++q) x_load(q, p, x_base(kx));
+  for (;;) {
+    const bool more = tix + wx < c1;
+    const Tile nxt = tile_of(more ? tix + wx : tix);  // (without a next tile: its own start again, never used)
+    const int k0 = cur.sp * (tl.k_len / 32);
+    const int nk = (min(K, (cur.sp + 1) * tl.k_len) / 32) - k0;  // a multiple of DX (checked by the launcher)
+    // the first k-steps' operands have landed, and the last tile's stores
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    // (read again here, so that they are not held through the epilogue)
+#pragma unroll
+    for (int i = 0; i < MB; ++i) fa[i] = frag[i * 64];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        asm volatile("" : "+a"(acc[i][j]));
+      }
+    asm volatile("s_nop 3");
+    // k-step k (stage k % DX): W(k) and X(k + 1) have landed for every wave
+    // after the wait and the barrier.  Its MFMAs, with W(k + AW) going into
+    // the registers W(k - 1) used, X(k + AX) into the stage X(k - 1) used
+    // (every wave has multiplied it before the barrier) and the fragments of
+    // X(k + 1) read into their places.  Past the tile's end the loads are the
+    // next tile's.
+    for (int kt = 0; kt < nk; kt += DX) {
+      const bool last = kt + DX >= nk;
+#pragma unroll
+      for (int s = 0; s < DX; ++s) {
+        constexpr int keep_w = (AW - 1) * PER + LX, keep_x = (AX - 2) * PER;  // loads newer than W(k), X(k + 1)
+        constexpr int keep = keep_w < keep_x ? keep_w : keep_x;
+        static_assert(keep <= 63, "vmcnt");
+        if (s == DX - AX && last) {
+          set_x(nxt.mt);
+          kx = nxt.sp * (tl.k_len / 32);
+        }
+        if (s == DX - AW && last) {
+          set_w(nxt.nt);
+          kw = nxt.sp * (tl.k_len / 32);
+        }
+        const char* xb = x_base(kx++);
+        const char* wb = w_base(kw++);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(keep) : "memory");
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_s_barrier();
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        const lds_units next = (s + 1) % DX < LOW ? frag + ((s + 1) % DX) * XU : frag_hi + ((s + 1) % DX - LOW) * XU;
+#pragma unroll
+        for (int u = 0; u < NM; ++u) {
+          const int i = u / NB, j = u % NB;
+          mfma_acc_bare(acc[i][j], fa[i], wr[s % DW][j]);
+          if (j == NB - 1) fa[i] = next[i * 64];
+          if (u % GAP == 1 && u / GAP < PER) {
+            const int q = u / GAP;
+            if (q < NB) load_reg16(wr[(s + AW) % DW][q], wb, wo[q]);
+            else x_load(q - NB, (s + AX) % DX, xb);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    // (the compiler does not know that the accumulators come from MFMAs)
+    asm volatile("s_nop 15\n\ts_nop 7");
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) asm volatile("" : "+a"(acc[i][j]));
+
+    // Lane (l16, g) holds rows 4 g + r of column l16 of each 16 x 16 block;
+    // after the quad transpose row 4 g + l16 % 4, columns 4 (l16 / 4) .. + 3.
+    // The residual rows are read kM4Pre row blocks ahead (with each block's
+    // loads behind the last one's stores the 4096-row O projection's add took
+    // 45 of 180 thousand cycles).
+    const int m0 = cur.mt * TM, f0 = cur.nt * (SW ? 8 * NTG : 16 * NTG);
+    const int q4 = l16 & 3, c4 = (l16 >> 2) * 4;
+    if (part) {  // split K: partials by W row (gate rows, then up rows)
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        const int m = m0 + 16 * i + 4 * g + q4;
+        float* pr = part + (static_cast<size_t>(cur.sp) * R + m) * (SW ? 2 * N : N);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+          float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+          quad_transpose(v);
+          const int n = f0 + 16 * (SW ? wave * (NB / 2) + j % (NB / 2) : wave * NB + j) + c4;
+          if (m < R && n < N)
+            *reinterpret_cast<float4*>(pr + (SW && j >= NB / 2 ? N : 0) + n) = make_float4(v[0], v[1], v[2], v[3]);
+        }
+      }
+    } else {
+      constexpr bool ADD = EPI == kEpiAddF32;
+      constexpr int NO = SW ? NB / 2 : NB, PRE = 4;
+      float4 h[ADD ? PRE : 1][NO];
+      auto col = [&](int j) { return f0 + 16 * (SW ? wave * (NB / 2) + j : wave * NB + j) + c4; };
+      auto load_h = [&](int i) {
+        const float* y = static_cast<const float*>(Y) + static_cast<size_t>(min(m0 + 16 * i + 4 * g + q4, R - 1)) * N;
+#pragma unroll
+        for (int j = 0; j < NO; ++j) h[i % PRE][j] = *reinterpret_cast<const float4*>(y + min(col(j), N - 4));
+      };
+      if constexpr (ADD) {
+#pragma unroll
+        for (int i = 0; i < PRE; ++i) load_h(i);
+      }
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        const int m = m0 + 16 * i + 4 * g + q4;
+        float o[NO][4];
+#pragma unroll
+        for (int j = 0; j < NO; ++j) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            o[j][r] = SW ? silu(acc[i][j][r]) * acc[i][(j + NB / 2) % NB][r] : acc[i][j][r];
+          quad_transpose(o[j]);
+          if constexpr (ADD) {
+            const float4 hv = h[i % PRE][j];
+            o[j][0] += hv.x;
+            o[j][1] += hv.y;
+            o[j][2] += hv.z;
+            o[j][3] += hv.w;
+          }
+        }
+        if constexpr (ADD) {
+          if (i + PRE < MB) load_h(i + PRE);
+        }
+        const size_t mo = (EPI == kEpiStoreF32 && row_map && m < R) ? static_cast<size_t>(row_map[m])
+                                                                     : static_cast<size_t>(m);
+#pragma unroll
+        for (int j = 0; j < NO; ++j) {
+          const int n = col(j);
+          if (m >= R || n >= N) continue;
+          if (SW)
+            *reinterpret_cast<uint2*>(static_cast<bf16_t*>(Y) + mo * N + n) =
+                make_uint2(cvt_pk_bf16(o[j][0], o[j][1]), cvt_pk_bf16(o[j][2], o[j][3]));
+          else
+            *reinterpret_cast<float4*>(static_cast<float*>(Y) + mo * N + n) =
+                make_float4(o[j][0], o[j][1], o[j][2], o[j][3]);
+        }
+      }
+    }
+    if (!more) break;
+    tix += wx;
+    cur = nxt;
+  }
+  // the loads past the last tile land before their registers are reused
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int s = 0; s < DW; ++s)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) asm volatile("" ::"v"(wr[s][j]));
+}
+
 // Sum split-K partials [S][R][Nw] in split order and apply the epilogue.
 template <int EPI>
 __global__ __launch_bounds__(256) void splitk_reduce(const float* __restrict__ part, int S, int R, int N,
@@ -1360,14 +1651,13 @@ hipError_t mfma2_m(int ntw, int R, int N, int K, const bf16_t* x, const bf16_t* 
 }
 
 // gemm_mfma3_bf16 (weights straight to registers), 192 x 256 tiles for the
-// shapes it was measured to win: SwiGLU gate/up from 160 rows in one pass
-// (364-row serving verify 114 -> 97 us, 2048-row prefill 508 -> 433 us, 8192
-// rows 1966 -> 1641 us), store-only projections of 65536+ rows in one pass
-// (the LM head: 425 -> 404 us at 364 rows), each when the tiles fill the 256
-// CUs at least 3 / 4 of the way; and residual-add projections with K >= 8192
-// whose grid splits K (the 364-row down projection: 76 -> 64 us).  Elsewhere
-// (the QKV and O projections, the unsplit 2048-row down projection)
-// gemm_mfma2_bf16 was as fast or faster.
+// shapes where it beats gemm_mfma2_bf16, of those that gemm_mfma4_bf16 leaves
+// (residual adds of 4096+ outputs up to 384 rows; K % 256 != 0, a partial W
+// tile or an unaligned output): residual-add projections with K >= 8192 whose
+// grid splits K (the 364-row down projection: 76 -> 64 us), and SwiGLU from
+// 160 rows and store-only projections of 65536+ rows in one pass when the
+// tiles fill the 256 CUs at least 3 / 4 of the way (364-row gate/up 114 -> 97
+// us).
 constexpr int kM3MB = 12, kM3NB = 4, kM3D = 4;
 // Small form: 64-row tiles (MB 4) of 64 NB W rows, K split to fill the CUs,
 // for the drafter's and the target's 41-128-row projections, where every
@@ -1461,11 +1751,118 @@ hipError_t mfma3(int R, int N, int K, const bf16_t* x, const bf16_t* w, void* Y,
   return splitk_finish<EPI>(ws, p.S, R, N, Y, st, rm, norm);
 }
 
+// ---------------------------------------------------------------------------
+// gemm_mfma4_bf16's tile shape and K split.
+
+struct M4Shape {
+  int mb, nb, occ;      // tile 16 mb rows x 64 nb W rows, workgroups per CU
+  double step, rounds;  // us per 1000 MFMA cycles of a k-step; factor where a launch has several rounds
+};
+// 256 x 256 down to 64 x 128: fewer bytes per flop against more workgroups.
+constexpr M4Shape kM4Shapes[] = {{16, 4, 1, 0.64, 1.0},  {16, 3, 1, 0.62, 1.0},  {12, 4, 1, 0.65, 1.06},
+                                 {8, 4, 1, 0.68, 1.16}, {8, 2, 2, 0.76, 1.16}, {4, 2, 2, 0.90, 1.16}};
+constexpr int kM4Shapes_n = sizeof(kM4Shapes) / sizeof(kM4Shapes[0]);
+
+struct M4Plan {
+  int shape = -1;
+  M4Tiles tl{};
+};
+
+// Estimated time in us, a fit (median error 8%) to 3000 launches of every
+// shape and split on 15 projections at 100 to 8192 rows: a k-step takes the
+// longer (4-norm) of its MFMAs and of its X and W bytes at 80 GB/s per CU
+// (the most a CU takes in), over whole rounds of workgroups; then the output
+// at 4.3 TB/s, and for a split the second pass.  The shape it picks is within
+// 1.1% of the best one on average, 3.6% at the ninetieth percentile.
+double m4_time(const M4Shape& s, int R, int N, int Nw, int K, int epi, int S, bool normed, bool deferred) {
+  const int MT = (R + 16 * s.mb - 1) / (16 * s.mb), NT = (Nw + 64 * s.nb - 1) / (64 * s.nb);
+  const int k_len = ((K + S - 1) / S + 255) / 256 * 256;
+  const int T = MT * NT * S, cap = 256 * s.occ;
+  const double steps = k_len / 32;
+  const double mfma = s.mb * s.nb * 0.016 * s.step;
+  const double in = (std::min(16 * s.mb, R) + 64 * s.nb) * 0.064 * 0.0125;
+  const double tile_mb = 16.0 * s.mb * 64.0 * s.nb * 4e-6 *
+                         (S > 1 ? 1.0 : epi == kEpiAddF32 ? 2.0 : epi == kEpiSwiGLU ? 0.25 : 1.0);
+  auto round = [&](int n) {  // n workgroups at once
+    const double a = n > 256 ? 2.0 * 1.15 * mfma : mfma, b = n > 256 ? 2.0 * in : in;
+    return steps * std::sqrt(std::sqrt(a * a * a * a + b * b * b * b)) + 0.23 * tile_mb * n;
+  };
+  double t = (T / cap) * round(cap) + (T % cap ? round(T % cap) : 0.0);
+  if (T > cap) t *= s.rounds;
+  const double out = R * static_cast<double>(N) / 1e6, part = R * static_cast<double>(Nw) * S / 1e6;
+  if (S > 1) t += deferred ? 0.3 * part : 4.5 + 0.375 * (part + 2.0 * out);
+  else if (normed) t += 3.0 + 1.5 * out;  // the RMSNorm that a split's second pass applies
+  return t;
+}
+
+// Rows above 128 (below, gemm_mfma3_bf16's 64-row form is as fast) of
+// projections of whole W tiles and whole unrolled k-loops.  Residual adds of
+// 4096+ outputs stay with gemm_mfma3_bf16 up to 384 rows: both are bound by
+// what a CU takes in there (382-row down projection 63.7 against 64.1 us, O
+// 26.9 against 25.6-26.0).
+bool plan_mfma4(int R, int N, int K, int epi, size_t ws_bytes, bool normed, bool deferred, M4Plan* plan = nullptr) {
+  const int Nw = epi == kEpiSwiGLU ? 2 * N : N;
+  if (R <= 128 || N % 16 || K % (32 * kM4DX)) return false;
+  if (static_cast<double>(Nw) * K >= 2147483648.0 || static_cast<double>(R) * K >= 2147483648.0) return false;
+  if (epi == kEpiAddF32 && N >= 4096 && R <= 384 && ws_bytes) return false;
+  double best = 1e300;
+  for (int i = 0; i < kM4Shapes_n; ++i) {
+    const M4Shape& s = kM4Shapes[i];
+    if (epi == kEpiSwiGLU && s.nb % 2) continue;
+    const int MT = (R + 16 * s.mb - 1) / (16 * s.mb), NT = (Nw + 64 * s.nb - 1) / (64 * s.nb);
+    for (int S = 1; S <= 8; S *= 2) {
+      const int k_len = ((K + S - 1) / S + 255) / 256 * 256;
+      if (S > 1 && ((K + k_len - 1) / k_len != S || MT * NT * S > 512 * s.occ ||
+                    static_cast<size_t>(S) * R * Nw * sizeof(float) > ws_bytes))
+        continue;
+      const double t = m4_time(s, R, N, Nw, K, epi, S, normed, deferred);
+      if (t < best) {
+        best = t;
+        if (plan) *plan = {i, {MT, NT, S, k_len}};
+      }
+    }
+  }
+  return true;
+}
+
+template <int EPI>
+hipError_t mfma4(int R, int N, int K, const bf16_t* x, const bf16_t* w, void* Y, hipStream_t st, const int32_t* rm,
+                 float* ws, const M4Plan& p, GemmNorm* norm) {
+  using Kern = void (*)(const bf16_t*, const bf16_t*, void*, float*, int, int, int, M4Tiles, const int32_t*);
+  Kern k = nullptr;
+  switch (p.shape) {
+    case 0: k = gemm_mfma4_bf16<EPI, 16, 4, 1>; break;
+    case 1:
+      if constexpr (EPI != kEpiSwiGLU) k = gemm_mfma4_bf16<EPI, 16, 3, 1>;
+      break;
+    case 2: k = gemm_mfma4_bf16<EPI, 12, 4, 1>; break;
+    case 3: k = gemm_mfma4_bf16<EPI, 8, 4, 1>; break;
+    case 4: k = gemm_mfma4_bf16<EPI, 8, 2, 2>; break;
+    case 5: k = gemm_mfma4_bf16<EPI, 4, 2, 2>; break;
+    default: break;
+  }
+  if (!k) return hipErrorInvalidValue;
+  const int grid = std::min(256 * kM4Shapes[p.shape].occ, p.tl.MT * p.tl.NT * p.tl.S);
+  if (p.tl.S <= 1) {
+    launch_kernel(k, dim3(grid), dim3(256), 0, st, x, w, Y, static_cast<float*>(nullptr), R, N, K, p.tl, rm);
+    return hipGetLastError();
+  }
+  launch_kernel(k, dim3(grid), dim3(256), 0, st, x, w, static_cast<void*>(nullptr), ws, R, N, K, p.tl, rm);
+  return splitk_finish<EPI>(ws, p.tl.S, R, N, Y, st, rm, norm);
+}
+
 template <int EPI>
 hipError_t mfma2(int R, int N, int K, const void* X, const void* W, void* Y, hipStream_t st,
                  const int32_t* rm, float* ws, size_t ws_bytes, GemmNorm* norm = nullptr) {
   const bf16_t* x = static_cast<const bf16_t*>(X);
   const bf16_t* w = static_cast<const bf16_t*>(W);
+  // gemm_mfma4_bf16 moves 4 outputs (and partials) at a time
+  const auto aligned = [](const void* p, unsigned a) { return reinterpret_cast<uintptr_t>(p) % a == 0; };
+  M4Plan p4;
+  if (aligned(Y, EPI == kEpiSwiGLU ? 8 : 16) &&
+      plan_mfma4(R, N, K, EPI, ws && aligned(ws, 16) ? ws_bytes : 0, EPI == kEpiAddF32 && norm && !rm,
+                 EPI == kEpiStoreF32 && norm && norm->defer && !rm, &p4))
+    return mfma4<EPI>(R, N, K, x, w, Y, st, rm, ws, p4, norm);
   Mfma3Plan p3;
   if (use_mfma3(R, EPI == kEpiSwiGLU ? 2 * N : N, K, EPI, ws ? ws_bytes : 0, &p3))
     return mfma3<EPI>(R, N, K, x, w, Y, st, rm, ws, p3, norm);
@@ -1554,7 +1951,8 @@ hipError_t launch_gemm_fused(int R, int N, int K, const void* X, const void* W, 
   }
 }
 
-const char* gemm_kernel_name(int dtype, int R, int N, int K, int epi, bool fused, size_t splitk_bytes) {
+const char* gemm_kernel_name(int dtype, int R, int N, int K, int epi, bool fused, size_t splitk_bytes, bool normed,
+                             bool deferred) {
   static const char* gv[4] = {"gemv_bf16<0, 2, false>", "gemv_bf16<1, 2, false>", "gemv_bf16<2, 2, false>",
                               "gemv_bf16<3, 2, false>"};
   if (dtype == 1 && R <= kGemvRows && !(fused && gemv_lm_skinny(R, N, K, epi)))
@@ -1593,6 +1991,16 @@ const char* gemm_kernel_name(int dtype, int R, int N, int K, int epi, bool fused
           snprintf(m3[e][nb], sizeof(m3[e][nb]), "gemm_mfma3_bf16<%d, %d, %d, %d>", e, kM3sMB, nb, kM3D);
       }
     });
+    static char m4[3][kM4Shapes_n][40];
+    static std::once_flag once4;
+    std::call_once(once4, [] {
+      for (int e = 0; e < 3; ++e)
+        for (int i = 0; i < kM4Shapes_n; ++i)
+          snprintf(m4[e][i], sizeof(m4[e][i]), "gemm_mfma4_bf16<%d, %d, %d, %d>", e, kM4Shapes[i].mb, kM4Shapes[i].nb,
+                   kM4Shapes[i].occ);
+    });
+    M4Plan p4;
+    if (plan_mfma4(R, N, K, epi, splitk_bytes, normed, deferred, &p4)) return m4[epi][p4.shape];
     Mfma3Plan p3;
     if (use_mfma3(R, Nw, K, epi, splitk_bytes, &p3)) return m3[epi][p3.nb];
     const Mfma2Shape sh = mfma2_shape(R, N, Nw, K, splitk_bytes, epi == kEpiSwiGLU);
