@@ -35,6 +35,7 @@ inline void launch_kernel(F kernel, dim3 grid, dim3 block, size_t lds, hipStream
 typedef uint16_t bf16_t;  // storage type: bf16 bit pattern
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));  // 16 bytes of global memory at any float
 
 constexpr int kWave = 64;
 constexpr int kPage = 16;

@@ -1510,6 +1510,126 @@ __global__ __launch_bounds__(256) void gemm_f32(const float* __restrict__ X,
   }
 }
 
+// The same on matrix cores for K % 4 == 0: v_mfma_f32_16x16x4_f32, fp32 products and sums.  A workgroup owns
+// 16 MB rows x 16 NB features (SwiGLU: the gate and the up features); its 4
+// waves take every fourth 16-column chunk of K and add up through LDS in wave
+// order.  Lane (l16, g) of a chunk loads columns 4 g .. + 3 of row l16 of X
+// and of W, and MFMA e multiplies element e of every lane: one 16-byte load
+// of each feeds four MFMAs, and the loads of kF32Unroll chunks are in flight
+// together.  Small models are latency here (a few hundred KB of weights):
+// 16 x 16 tiles give a 5-row projection of 768 features 48 workgroups of
+// independent loads instead of 12 that walk K in steps of 16 behind barriers
+// (5 rows, K 688: 75 -> 5 us); 32 x 32 tiles once those fill the chip.
+constexpr int kF32Unroll = 4;
+
+template <int EPI, int MB, int NB>
+__global__ __launch_bounds__(256) void gemm_mfma_f32(const float* __restrict__ X, const float* __restrict__ W,
+                                                     void* __restrict__ Y, int R, int N, int K,
+                                                     const int32_t* __restrict__ row_map) {
+  constexpr bool SW = (EPI == kEpiSwiGLU);
+  constexpr int NS = SW ? 2 : 1;
+  constexpr int NACC = MB * NB * NS;
+  constexpr int U = kF32Unroll;
+  __shared__ float red[4][NACC][4][kWave];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int g = lane >> 4, l16 = lane & 15;
+  const int m0 = blockIdx.y * 16 * MB, f0 = blockIdx.x * 16 * NB;
+  const float* xr[MB];
+  const float* wp[NB][NS];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) xr[i] = X + static_cast<size_t>(min(m0 + 16 * i + l16, R - 1)) * K;
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int h = 0; h < NS; ++h)
+      wp[j][h] = W + (static_cast<size_t>(h) * N + min(f0 + 16 * j + l16, N - 1)) * K;
+  f32x4 acc[MB][NB][NS];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int h = 0; h < NS; ++h) acc[i][j][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c0 = 16 * wave; c0 < K; c0 += 64 * U) {
+    f32x4 x[U][MB], w[U][NB][NS];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = c0 + 64 * u + 4 * g;
+      const bool in = k < K;  // whole float4s: K % 4 == 0
+      const int kc = in ? k : 0;
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        x[u][i] = *reinterpret_cast<const f32x4_any*>(xr[i] + kc);
+        if (!in) x[u][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int h = 0; h < NS; ++h) {
+          w[u][j][h] = *reinterpret_cast<const f32x4_any*>(wp[j][h] + kc);
+          if (!in) w[u][j][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int h = 0; h < NS; ++h)
+              acc[i][j][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u][i][e], w[u][j][h][e], acc[i][j][h], 0, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int h = 0; h < NS; ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[wave][(i * NB + j) * NS + h][r][lane] = acc[i][j][h][r];
+  __syncthreads();
+  // wave w finishes element r = w of every lane
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int m = m0 + 16 * i + 4 * g + wave, n = f0 + 16 * j + l16;
+      const int a = (i * NB + j) * NS;
+      float v = red[0][a][wave][lane], up = SW ? red[0][a + NS - 1][wave][lane] : 0.f;
+#pragma unroll
+      for (int s = 1; s < 4; ++s) {
+        v += red[s][a][wave][lane];
+        if (SW) up += red[s][a + NS - 1][wave][lane];
+      }
+      if (m >= R || n >= N) continue;
+      float* y = static_cast<float*>(Y) + static_cast<size_t>(row_map ? row_map[m] : m) * N + n;
+      if (EPI == kEpiStoreF32) *y = v;
+      if (EPI == kEpiAddF32) *y += v;
+      if (SW) *y = v / (1.f + expf(-v)) * up;
+    }
+}
+
+// 32 x 32 tiles from two workgroups per CU on
+bool f32_wide(int R, int N) { return static_cast<long long>((R + 31) / 32) * ((N + 31) / 32) >= 512; }
+
+template <int EPI>
+hipError_t gemm_fp32(int R, int N, int K, const float* X, const float* W, void* Y, hipStream_t st,
+                     const int32_t* rm) {
+  if (K % 4 == 0) {
+    if (f32_wide(R, N))
+      gemm_mfma_f32<EPI, 2, 2><<<dim3((N + 31) / 32, (R + 31) / 32), 256, 0, st>>>(X, W, Y, R, N, K, rm);
+    else
+      gemm_mfma_f32<EPI, 1, 1><<<dim3((N + 15) / 16, (R + 15) / 16), 256, 0, st>>>(X, W, Y, R, N, K, rm);
+    return hipGetLastError();
+  }
+  const int ncols = (EPI == kEpiSwiGLU) ? 32 : 64;
+  gemm_f32<EPI><<<dim3((N + ncols - 1) / ncols, (R + 63) / 64), 256, 0, st>>>(X, W, Y, R, N, K, rm);
+  return hipGetLastError();
+}
+
 // Waves per workgroup of the skinny kernel: 8 split K when there are few
 // tiles, else 4 (measured on the 8B/1B-shaped projections at 6 rows).
 int skinny_waves(int tiles, int K) { return (tiles <= 512 && K >= 2048) ? 8 : 4; }
@@ -1889,13 +2009,8 @@ bool use_mfma(int R, int Nw, int K) {
 template <int EPI>
 hipError_t dispatch(int dtype, int R, int N, int K, const void* X, const void* W, void* Y,
                     hipStream_t st, const int32_t* rm, float* ws, size_t ws_bytes, GemmNorm* norm = nullptr) {
-  if (dtype == 0) {
-    const int ncols = (EPI == kEpiSwiGLU) ? 32 : 64;
-    dim3 grid((N + ncols - 1) / ncols, (R + 63) / 64);
-    gemm_f32<EPI><<<grid, 256, 0, st>>>(static_cast<const float*>(X), static_cast<const float*>(W),
-                                        Y, R, N, K, rm);
-    return hipGetLastError();
-  }
+  if (dtype == 0)
+    return gemm_fp32<EPI>(R, N, K, static_cast<const float*>(X), static_cast<const float*>(W), Y, st, rm);
   if (K % 128 != 0) return hipErrorInvalidValue;
   if (R <= kGemvRows) return gemv<EPI>(R, N, K, X, W, Y, st, rm, GemmFuse{});
   if (use_mfma(R, EPI == kEpiSwiGLU ? 2 * N : N, K)) return mfma2<EPI>(R, N, K, X, W, Y, st, rm, ws, ws_bytes, norm);
@@ -1971,6 +2086,9 @@ const char* gemm_kernel_name(int dtype, int R, int N, int K, int epi, bool fused
   if (fused) return names[0][epi][1];
   if (epi > 2) return "";
   static const char* f32[3] = {"gemm_f32<0>", "gemm_f32<1>", "gemm_f32<2>"};
+  static const char* f32m[3][2] = {{"gemm_mfma_f32<0, 1, 1>", "gemm_mfma_f32<0, 2, 2>"},
+                                   {"gemm_mfma_f32<1, 1, 1>", "gemm_mfma_f32<1, 2, 2>"},
+                                   {"gemm_mfma_f32<2, 1, 1>", "gemm_mfma_f32<2, 2, 2>"}};
   static char tiled[3][4][3][40];
   static std::once_flag once_t;
   std::call_once(once_t, [] {
@@ -1979,7 +2097,7 @@ const char* gemm_kernel_name(int dtype, int R, int N, int K, int epi, bool fused
         for (int n = 0; n < 3; ++n)
           snprintf(tiled[e][m][n], sizeof(tiled[e][m][n]), "gemm_mfma2_bf16<%d, %d, %d>", e, 2 * m + 2, 2 << n);
   });
-  if (dtype == 0) return f32[epi];
+  if (dtype == 0) return K % 4 ? f32[epi] : f32m[epi][f32_wide(R, N)];
   const int Nw = epi == kEpiSwiGLU ? 2 * N : N;
   if (use_mfma(R, Nw, K)) {
     static char m3[3][5][40];  // [epi][nb: 0 the 192-row form, 1, 2, 4]
