@@ -23,6 +23,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include <type_traits>
 
 #include "attention.h"
 #include "common.h"
@@ -45,8 +46,11 @@ template <int HD, int NT, int W, bool TREE>
 __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const AttnItem* __restrict__ items) {
   constexpr int DS = HD / 32;   // MFMA k-steps over the head dim
   constexpr int DT = HD / 16;   // 16-dim output tiles
-  const AttnItem it = items[blockIdx.x];
-  const int gkv = blockIdx.y;
+  // the kv heads of an item run side by side: their blocks of a page are one
+  // run of memory (loads alone, 64-sequence verify: 72-87 us with the items
+  // first, depending on the split, 71-73 us with the heads first)
+  const int gkv = blockIdx.x % a.Hkv;
+  const AttnItem it = items[blockIdx.x / a.Hkv];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int g = lane >> 4, l16 = lane & 15;
   const int G = a.Hq / a.Hkv;
@@ -65,7 +69,6 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const AttnItem
   if (staged)
     for (int i = threadIdx.x; i < np; i += kWave * W) s_pt[i] = pt[p0 + i];
   __syncthreads();
-  auto page = [&](int t) { return staged ? s_pt[(t >> 4) - p0] : pt[t >> 4]; };
 
   uint4 qf[NT][DS];
   int vpos[NT];
@@ -91,6 +94,8 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const AttnItem
       qf[nt][s] = vval[nt] ? reinterpret_cast<const uint4*>(base)[4 * s] : make_uint4(0, 0, 0, 0);
   }
   const float scale = kLog2e / sqrtf(static_cast<float>(HD));
+  // every row of the item sees the keys up to here
+  const int pos_lo = TREE ? a.tree_base[it.row0] : it.pos0;
   float mrun[NT], lrun[NT];
   f32x4 acc[DT][NT];
 #pragma unroll
@@ -101,112 +106,130 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const AttnItem
     for (int dt = 0; dt < DT; ++dt) acc[dt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
-  // K and V^T operands of one 32-key chunk (keys past t1 are clamped to a
-  // valid address; their scores are masked and their V entries zeroed)
-  auto load_k = [&](int c0, uint4 (&kf)[2][DS]) {
-    // lanes 0-7 / 8-15 of a group read the chunk's first / second page:
-    // unit ((s * 2 + hh) * 4 + g) * 8 + l16 % 8 of the page's K block holds
-    // dims 32 s + 8 g .. of key 8 (l16 / 4) + 4 hh + l16 % 4 (kv_layout.h)
-    const int tk = min(c0 + 16 * (l16 >> 3), it.t1 - 1);
-    const uint4* kb = reinterpret_cast<const uint4*>(kp + static_cast<size_t>(page(tk) * a.Hkv + gkv) * 16 * HD);
+  // The wave's chunks.  One K and one V^T buffer: the next chunk's K is loaded
+  // once this chunk's scores are computed, its V^T once this chunk's output
+  // update is done (loads are unconditional, clamped past the end, so that the
+  // compiler's waits stay exact), which keeps 16 KB of a head dim of 128 in
+  // flight per wave.  The page ids come from LDS or from the table in two
+  // instances of the loop: a choice per load made the compiler fetch them by
+  // flat loads, whose waits drained every load in flight twice a chunk (the
+  // 64-sequence verify ran at 4.6 TB/s).
+  auto walk = [&](auto from_lds) {
+    auto page = [&](int t) {
+      if constexpr (decltype(from_lds)::value) return s_pt[(t >> 4) - p0];
+      else return pt[t >> 4];
+    };
+    // K and V^T operands of one 32-key chunk (keys past t1 are clamped to a
+    // valid address; their scores are masked and their V entries zeroed)
+    auto load_k = [&](int c0, uint4 (&kf)[2][DS]) {
+      // lanes 0-7 / 8-15 of a group read the chunk's first / second page:
+      // unit ((s * 2 + hh) * 4 + g) * 8 + l16 % 8 of the page's K block holds
+      // dims 32 s + 8 g .. of key 8 (l16 / 4) + 4 hh + l16 % 4 (kv_layout.h)
+      const int tk = min(c0 + 16 * (l16 >> 3), it.t1 - 1);
+      const uint4* kb = reinterpret_cast<const uint4*>(kp + static_cast<size_t>(page(tk) * a.Hkv + gkv) * 16 * HD);
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh)
+      for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-      for (int s = 0; s < DS; ++s) kf[hh][s] = ld_stream(kb + ((s * 2 + hh) * 4 + g) * 8 + (l16 & 7));
-  };
-  auto load_v = [&](int c0, uint4 (&vf)[DT]) {
-    // V^T: unit (dt * 2 + g % 2) * 16 + l16 holds keys 8 (g % 2) .. + 7 of
-    // dim 16 dt + l16 of page (c0 + 8 g) / 16
-    const int tvc = min(c0 + 8 * g, it.t1 - 1);
-    const uint4* vb = reinterpret_cast<const uint4*>(vp + static_cast<size_t>(page(tvc) * a.Hkv + gkv) * HD * 16);
+        for (int s = 0; s < DS; ++s) kf[hh][s] = ld_stream(kb + ((s * 2 + hh) * 4 + g) * 8 + (l16 & 7));
+    };
+    auto load_v = [&](int c0, uint4 (&vf)[DT]) {
+      // V^T: unit (dt * 2 + g % 2) * 16 + l16 holds keys 8 (g % 2) .. + 7 of
+      // dim 16 dt + l16 of page (c0 + 8 g) / 16
+      const int tvc = min(c0 + 8 * g, it.t1 - 1);
+      const uint4* vb = reinterpret_cast<const uint4*>(vp + static_cast<size_t>(page(tvc) * a.Hkv + gkv) * HD * 16);
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) vf[dt] = ld_stream(vb + (dt * 2 + (g & 1)) * 16 + l16);
-  };
-  // One K and one V^T buffer: the next chunk's K is loaded once this chunk's
-  // scores are computed, its V^T once this chunk's output update is done
-  // (loads are unconditional, clamped past the end, so that the compiler's
-  // waits stay exact).
-  uint4 kf[2][DS], vf[DT];
-  const int cfirst = it.t0 + 32 * wave;
-  if (cfirst < it.t1) {
-    load_k(cfirst, kf);
-    load_v(cfirst, vf);
-  }
-  for (int c0 = cfirst; c0 < it.t1; c0 += 32 * W) {
-    const int cn = min(c0 + 32 * W, it.t1 - 1);
-    const int tv = c0 + 8 * g;
-    const int nvalid = min(max(it.t1 - tv, 0), 8);
-
-    f32x4 sc[NT][2];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      f32x4 s0 = f32x4{0.f, 0.f, 0.f, 0.f}, s1 = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < DS; ++s) {
-        s0 = mfma16x16x32(kf[0][s], qf[nt][s], s0);
-        s1 = mfma16x16x32(kf[1][s], qf[nt][s], s1);
-      }
-      sc[nt][0] = s0;
-      sc[nt][1] = s1;
+      for (int dt = 0; dt < DT; ++dt) vf[dt] = ld_stream(vb + (dt * 2 + (g & 1)) * 16 + l16);
+    };
+    uint4 kf[2][DS], vf[DT];
+    const int cfirst = it.t0 + 32 * wave;
+    if (cfirst < it.t1) {
+      load_k(cfirst, kf);
+      load_v(cfirst, vf);
     }
-    load_k(cn, kf);
-    uint4 pf[NT];
+    for (int c0 = cfirst; c0 < it.t1; c0 += 32 * W) {
+      const int cn = min(c0 + 32 * W, it.t1 - 1);
+      // every key inside the item and seen by every row: no masks
+      const bool full = c0 + 32 <= it.t1 && c0 + 31 <= pos_lo;
+      f32x4 sc[NT][2];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      float sv[8];
+      for (int nt = 0; nt < NT; ++nt) {
+        f32x4 s0 = f32x4{0.f, 0.f, 0.f, 0.f}, s1 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int t = c0 + 8 * g + j;
-        const float raw = (j < 4) ? sc[nt][0][j] : sc[nt][1][j - 4];
-        bool ok = vval[nt] && t < it.t1;
-        if constexpr (TREE) {
-          const int rel = t - vpos[nt];
-          ok = ok && (rel <= 0 || (rel <= 32 && ((tmask[nt] >> (rel - 1)) & 1u)));
-        } else {
-          ok = ok && t <= vpos[nt];
+        for (int s = 0; s < DS; ++s) {
+          s0 = mfma16x16x32(kf[0][s], qf[nt][s], s0);
+          s1 = mfma16x16x32(kf[1][s], qf[nt][s], s1);
         }
-        sv[j] = ok ? raw * scale : -INFINITY;
+        sc[nt][0] = s0;
+        sc[nt][1] = s1;
       }
-      float mx = sv[0];
+      load_k(cn, kf);
+      uint4 pf[NT];
 #pragma unroll
-      for (int j = 1; j < 8; ++j) mx = fmaxf(mx, sv[j]);
-      mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-      const float mnew = fmaxf(mrun[nt], mx);
-      float p[8];
-      float alpha = 1.f;
-      if (mnew == -INFINITY) {
+      for (int nt = 0; nt < NT; ++nt) {
+        float raw[8];  // raw scores, -inf where masked
 #pragma unroll
-        for (int j = 0; j < 8; ++j) p[j] = 0.f;
-      } else {
-        alpha = (mrun[nt] == -INFINITY) ? 0.f : exp2f(mrun[nt] - mnew);
+        for (int j = 0; j < 8; ++j) raw[j] = (j < 4) ? sc[nt][0][j] : sc[nt][1][j - 4];
+        if (!full) {
+          asm volatile("");  // keeps the masks a branch
 #pragma unroll
-        for (int j = 0; j < 8; ++j) p[j] = exp2f(sv[j] - mnew);
+          for (int j = 0; j < 8; ++j) {
+            const int t = c0 + 8 * g + j;
+            bool ok = vval[nt] && t < it.t1;
+            if constexpr (TREE) {
+              const int rel = t - vpos[nt];
+              ok = ok && (rel <= 0 || (rel <= 32 && ((tmask[nt] >> (rel - 1)) & 1u)));
+            } else {
+              ok = ok && t <= vpos[nt];
+            }
+            raw[j] = ok ? raw[j] : -INFINITY;
+          }
+        }
+        float mx = raw[0];
+#pragma unroll
+        for (int j = 1; j < 8; ++j) mx = fmaxf(mx, raw[j]);
+        mx *= scale;  // base-2 logit (scale > 0)
+        // a new maximum: the same in every lane of a query vector
+        if (__any(mx > mrun[nt])) {
+          mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
+          mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+          const bool grow = mx > mrun[nt];
+          const float alpha = grow ? ((mrun[nt] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mrun[nt] - mx)) : 1.f;
+          if (grow) mrun[nt] = mx;
+          lrun[nt] *= alpha;
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) acc[dt][nt] *= alpha;
+        }
+        const float mneg = (mrun[nt] == -INFINITY) ? -INFINITY : -mrun[nt];
+        float p[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) p[j] = __builtin_amdgcn_exp2f(fmaf(raw[j], scale, mneg));
+        float ps = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) ps += p[j];
+        lrun[nt] += ps;
+        pf[nt] = make_uint4(cvt_pk_bf16(p[0], p[1]), cvt_pk_bf16(p[2], p[3]), cvt_pk_bf16(p[4], p[5]),
+                            cvt_pk_bf16(p[6], p[7]));
       }
-      float ps = 0.f;
+      if (c0 + 32 > it.t1) {  // keys past the end hold anything, and 0 x NaN is not 0
+        asm volatile("");
+        const int nvalid = min(max(it.t1 - (c0 + 8 * g), 0), 8);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) ps += p[j];
-      lrun[nt] = lrun[nt] * alpha + ps;
-      mrun[nt] = mnew;
+        for (int dt = 0; dt < DT; ++dt) {
+          vf[dt].x = mask_pair(vf[dt].x, nvalid);
+          vf[dt].y = mask_pair(vf[dt].y, nvalid - 2);
+          vf[dt].z = mask_pair(vf[dt].z, nvalid - 4);
+          vf[dt].w = mask_pair(vf[dt].w, nvalid - 6);
+        }
+      }
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) acc[dt][nt] *= alpha;
-      pf[nt] = make_uint4(pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]),
-                          pack_bf16x2(p[4], p[5]), pack_bf16x2(p[6], p[7]));
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[dt][nt] = mfma16x16x32(vf[dt], pf[nt], acc[dt][nt]);
+      load_v(cn, vf);
     }
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-      uint4 v = vf[dt];
-      if (nvalid < 8) {
-        v.x = mask_pair(v.x, nvalid);
-        v.y = mask_pair(v.y, nvalid - 2);
-        v.z = mask_pair(v.z, nvalid - 4);
-        v.w = mask_pair(v.w, nvalid - 6);
-      }
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[dt][nt] = mfma16x16x32(v, pf[nt], acc[dt][nt]);
-    }
-    load_v(cn, vf);
-  }
+  };
+  if (staged) walk(std::true_type{});
+  else walk(std::false_type{});
 
   float ltot[NT];
 #pragma unroll
@@ -342,8 +365,8 @@ __global__ __launch_bounds__(64 * W, NT <= 2 ? 2 : 1) void attn_tree_bf16_kernel
 // accumulators.  Probabilities stay below 2^8 in between; the shared maximum
 // is the same in every lane of a query vector, so the products stay exact.
 // Chunks entirely at or below every row of a wave skip the causal mask.
-constexpr int kPrefillStagedPages = 1024;  // page ids kept in LDS (16384 keys)
 constexpr float kPrefillRescaleLog2 = 8.f;
+constexpr int kPrefillStagedPages = 1024;  // page ids kept in LDS (16384 keys)
 
 template <int HD>
 __global__ __launch_bounds__(512, 1) void attn_prefill_bf16_kernel(AttnArgs a, const AttnItem* __restrict__ items) {
@@ -742,7 +765,7 @@ void launch_item_kernel(const AttnArgs& a, const AttnItem* items, dim3 grid, int
 template <int HD>
 hipError_t launch_bf16_hd(const AttnArgs& a, const AttnItem* items, int n_items,
                           const AttnGroup* groups, int n_groups, int nt, int w, hipStream_t st) {
-  dim3 grid(n_items, a.Hkv);
+  dim3 grid(n_items * a.Hkv);
   if (n_items > 0) {
     if (nt <= 1) launch_item_kernel<HD, 1>(a, items, grid, w, st);
     else if (nt == 2) launch_item_kernel<HD, 2>(a, items, grid, w, st);
