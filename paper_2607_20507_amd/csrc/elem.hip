@@ -7,6 +7,7 @@
 
 #include "common.h"
 #include "elem.h"
+#include "host_util.h"
 #include "kv_layout.h"
 
 namespace spec {
@@ -22,6 +23,34 @@ __device__ __forceinline__ int k_index(int k, int d, int hd) {
 template <typename T>
 __device__ __forceinline__ int v_index(int k, int d) {
   return sizeof(T) == 2 ? kv_v_off(k, d) : d * 16 + k;
+}
+
+// Call tables (launch_upload_inline / launch_upload_mapped): one 16-byte unit
+// per thread, so that all of a table's reads over PCIe are in flight at once.
+// `n4` 4-byte words; the last unit may be partial.
+struct UploadArgs {
+  uint4 v[kUploadInline / 16];
+};
+__device__ __forceinline__ void store_words(uint32_t* dst, uint32_t i, uint32_t n4, const uint4& v) {
+  if (4 * i + 4 <= n4) {
+    reinterpret_cast<uint4*>(dst)[i] = v;
+    return;
+  }
+  dst[4 * i] = v.x;
+  if (4 * i + 1 < n4) dst[4 * i + 1] = v.y;
+  if (4 * i + 2 < n4) dst[4 * i + 2] = v.z;
+}
+__global__ __launch_bounds__(192) void upload_inline_kernel(UploadArgs a, uint32_t* __restrict__ dst, uint32_t n4) {
+  if (4 * threadIdx.x < n4) store_words(dst, threadIdx.x, n4, a.v[threadIdx.x]);
+}
+__global__ __launch_bounds__(256) void upload_mapped_kernel(const uint32_t* __restrict__ src,
+                                                            uint32_t* __restrict__ dst, uint32_t n4) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (4 * i + 4 <= n4) {
+    store_words(dst, i, n4, ld_stream(reinterpret_cast<const uint4*>(src) + i));
+  } else {
+    for (uint32_t k = 4 * i; k < n4; ++k) dst[k] = src[k];
+  }
 }
 
 template <typename T>
@@ -460,6 +489,23 @@ hipError_t launch_rope_kv(int dtype, int R, int Hq, int Hkv, int hd, float theta
     rope_kv_kernel<bf16_t, false><<<grid, 256, 0, st>>>(Hq, Hkv, hd, theta, qkv, pos, slot, static_cast<bf16_t*>(q),
                                                      static_cast<bf16_t*>(kpool), static_cast<bf16_t*>(vpool),
                                                      rot_tiled, 0, 0);
+  return hipGetLastError();
+}
+
+hipError_t launch_upload_inline(void* dst, const void* src, size_t n, hipStream_t st) {
+  if (n > kUploadInline || n % 4) return hipErrorInvalidValue;
+  static_assert(sizeof(UploadArgs) / 16 == 192, "one thread per unit");
+  UploadArgs a;
+  std::memcpy(&a, src, n);
+  upload_inline_kernel<<<1, 192, 0, st>>>(a, static_cast<uint32_t*>(dst), static_cast<uint32_t>(n / 4));
+  return hipGetLastError();
+}
+
+hipError_t launch_upload_mapped(void* dst, const void* src, size_t n, hipStream_t st) {
+  if (n % 4) return hipErrorInvalidValue;
+  const uint32_t n4 = static_cast<uint32_t>(n / 4);
+  upload_mapped_kernel<<<(n4 + 1023) / 1024, 256, 0, st>>>(static_cast<const uint32_t*>(src),
+                                                           static_cast<uint32_t*>(dst), n4);
   return hipGetLastError();
 }
 
