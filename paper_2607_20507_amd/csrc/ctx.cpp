@@ -81,7 +81,7 @@ struct Seq {
 };
 
 struct Ws {
-  size_t h = 0, y = 0, qkv = 0, q = 0, o = 0, u = 0, logits = 0, dq = 0, dtok = 0, rowtok = 0;
+  size_t h = 0, y = 0, qkv = 0, q = 0, o = 0, u = 0, logits = 0, dq = 0, dtok = 0, rowtok = 0, ang = 0;
   size_t part_o = 0, part_ml = 0, vocab = 0, draft = 0, meta = 0, gmeta = 0;
   size_t splitk = 0, splitk_bytes = 0, ss = 0;
   size_t meta_cap = 0, total = 0;
@@ -235,6 +235,7 @@ void compute_ws(spec_ctx* c) {
   w.dtok = take(nq * 4);
   w.rowtok = take(R * 4);
   w.ss = take(R * (c->d_max / 8 + 1) * 4);
+  w.ang = take(R * (c->hd_max / 2) * sizeof(float2));
   w.part_o = take(static_cast<size_t>(kMaxParts) * c->hkv_max * 64 * c->hd_max * 4);
   w.part_ml = take(static_cast<size_t>(kMaxParts) * c->hkv_max * 64 * 2 * 4);
   const int vrows = c->max_seqs * (2 * c->k_max + 1);
@@ -312,6 +313,21 @@ FwdOff add_forward(spec_ctx* ctx, const Model& M, const Fwd& f, MetaBlock& mb) {
   return o;
 }
 
+// Rows of the fused path: one 16-row MFMA block of any model; up to
+// kFusedMaxRows, a workgroup per 16 rows, where the layer's projections are at
+// most 16M weights, which the 8 L2s (32 MB) hold while the row blocks read
+// them.  Measured forward against five more launches a layer (RMSNorms in the
+// split-K reductions, rope_kv, the SwiGLU's second pass), contexts 400: 12
+// layers of 1024 x 5632 at 10 / 32 / 64 rows 459 / 594 / 680 -> 414 / 500 /
+// 551 us; 16 layers of 2048 x 16384 at 10 / 16 rows 981 / 1083 -> 852 / 1000,
+// but at 18 and 48 rows 1124 -> 1204 and 1232 -> 1541 us; 4 layers of 4096 x
+// 28672 at 10 / 16 rows 608 / 696 -> 581 / 638, at 18 rows 726 -> 920 us.  (Whole
+// rows per workgroup, W read once: 1232 -> 1595 us at 48 rows, since every
+// 16-feature tile takes in all of X.)  The LM head stays with the tiled GEMM
+// from 9 rows on (16 layers of 2048 x 16384 at 10 rows: 852 us, fused 882).
+constexpr int kFusedRows = 16, kFusedLmRows = 8;
+constexpr long long kFusedSmallWeights = 16LL << 20;
+
 spec_status launch_forward(spec_ctx* ctx, const Model& M, const FwdOff& o, const char* dev,
                            float* logits, hipStream_t st) {
   const int dt = M.dt();
@@ -324,16 +340,24 @@ spec_status launch_forward(spec_ctx* ctx, const Model& M, const FwdOff& o, const
   void* q = ctx->wsp + ctx->ws.q;
   void* ob = ctx->wsp + ctx->ws.o;
   void* u = ctx->wsp + ctx->ws.u;
-  // Up to 8 rows (batch-1 verify and draft steps) RMSNorm and RoPE / KV
-  // append run inside the GEMMs (launch_gemm_fused): each residual-add GEMM
-  // (and the embedding) also writes bf16(h (.) w_next) into y and per-8-column
-  // sums of squares into ss; the next GEMM reads y and scales its output rows
-  // by 1/rms; the QKV GEMM applies RoPE and writes q and the KV cache itself.
-  const bool fused = dt == 1 && R <= 8 && d.head_dim % 16 == 0 && d.d_model % 16 == 0;
+  // For few rows RMSNorm and RoPE / KV append run inside the GEMMs
+  // (launch_gemm_fused): each residual-add GEMM (and the embedding) also
+  // writes bf16(h (.) w_next) into y and per-8-column sums of squares into ss;
+  // the next GEMM reads y and scales its output rows by 1/rms; the QKV GEMM
+  // applies RoPE and writes q and the KV cache itself.
+  const long long most = std::max({static_cast<long long>(M.qkvw()) * d.d_model, 2LL * d.ffn_dim * d.d_model,
+                                   static_cast<long long>(M.qdim()) * d.d_model});
+  const int fused_rows = most <= kFusedSmallWeights ? kFusedMaxRows : kFusedRows;
+  const bool fused = dt == 1 && R <= fused_rows && d.head_dim % 16 == 0 && d.d_model % 16 == 0;
   float* ss = wsptr<float>(ctx, ctx->ws.ss);
+  RotTable rot;
+  rot.ang = wsptr<float2>(ctx, ctx->ws.ang);
+  rot.pos = I(o.pos);
+  rot.hd = d.head_dim;
+  rot.theta = d.rope_theta;
   HIPC(launch_embed(dt, R, d.d_model, I(o.tok), wsptr<int32_t>(ctx, ctx->ws.dtok), d.embed, h,
                     wsptr<int32_t>(ctx, ctx->ws.rowtok), st, fused ? y : nullptr,
-                    fused ? M.layers[0].attn_norm : nullptr, fused ? ss : nullptr));
+                    fused ? M.layers[0].attn_norm : nullptr, fused ? ss : nullptr, rot));
   AttnArgs a;
   a.dtype = dt;
   a.Hq = d.n_heads;
@@ -382,8 +406,7 @@ spec_status launch_forward(spec_ctx* ctx, const Model& M, const FwdOff& o, const
       fq.Hq = d.n_heads;
       fq.Hkv = d.n_kv_heads;
       fq.hd = d.head_dim;
-      fq.theta = d.rope_theta;
-      fq.pos = I(o.pos);
+      fq.ang = rot.ang;
       fq.slot = I(o.slot);
       fq.qout = q;
       fq.kpool = M.kl(l);
@@ -397,7 +420,7 @@ spec_status launch_forward(spec_ctx* ctx, const Model& M, const FwdOff& o, const
       HIPC(gemm(R, M.qkvw(), d.d_model, y, L.wqkv, qkv, kEpiStoreF32, nullptr, nullptr, &defer));
       HIPC(launch_rope_kv(dt, R, d.n_heads, d.n_kv_heads, d.head_dim, d.rope_theta,
                           defer.split > 0 ? defer.part : qkv, I(o.pos), I(o.slot), q, M.kl(l), M.vl(l), st,
-                          dt == 1, defer.split));
+                          dt == 1, defer.split, rot.ang));
     }
     a.kpool = M.kl(l);
     a.vpool = M.vl(l);
@@ -453,7 +476,7 @@ spec_status launch_forward(spec_ctx* ctx, const Model& M, const FwdOff& o, const
     // the fused GEMM takes whole 16-row tiles of W: a vocabulary that is not a
     // multiple of 16 goes through the row-gathering RMSNorm and the plain GEMM
     // (h holds the residual stream either way)
-    if (fused && d.vocab % 16 == 0) {
+    if (fused && d.vocab % 16 == 0 && o.n_lm <= kFusedLmRows) {
       GemmFuse fl;
       fl.ss = ss;
       fl.xrow = I(o.lmr);

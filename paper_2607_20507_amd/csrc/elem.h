@@ -9,10 +9,18 @@ namespace spec {
 // h[r] = E[tok(r)] (fp32), tok(r) = tok_src[r] if >= 0 else tok_pool[-1 - tok_src[r]];
 // the resolved ids are written to row_tok[r].  Optional (for the fused GEMMs'
 // RMSNorm): hb[r] = h[r] (.) wn in the model dtype, and ss[r][j] = the sum of
-// squares of h[r][8 j .. 8 j + 7] (d % 16 == 0).
+// squares of h[r][8 j .. 8 j + 7] (d % 16 == 0).  With rot.ang, also the
+// rotation angles of every row for the layers that follow:
+// ang[r][i] = (cos, sin)(pos[r] * theta^(-2i/hd)), evaluated in fp64.
+struct RotTable {
+  float2* ang = nullptr;  // [R][hd / 2]
+  const int32_t* pos = nullptr;
+  int hd = 0;
+  float theta = 0.f;
+};
 hipError_t launch_embed(int dtype, int R, int d, const int32_t* tok_src, const int32_t* tok_pool,
                         const void* E, float* h, int32_t* row_tok, hipStream_t st, void* hb = nullptr,
-                        const void* wn = nullptr, float* ss = nullptr);
+                        const void* wn = nullptr, float* ss = nullptr, const RotTable& rot = RotTable{});
 
 // y[i] = h[src(i)] / sqrt(mean(h^2) + eps) * w, src(i) = row_idx ? row_idx[i] : i.
 hipError_t launch_rmsnorm(int dtype, int R, int d, const float* h, const int32_t* row_idx,
@@ -28,11 +36,13 @@ hipError_t launch_rmsnorm(int dtype, int R, int d, const float* h, const int32_t
 // holds that many split-K partials [splits][R][width] of the QKV GEMM (the
 // deferred reduction of GemmNorm::defer), summed here in split order; the
 // columns of one KV head group ((Hq / Hkv + 2) hd floats, hd % 4 == 0) are
-// staged in LDS.  One workgroup per (row, KV head).
+// staged in LDS.  One workgroup per (row, KV head).  ang: the rows' angles
+// from launch_embed (pos and theta unused), null to evaluate them here.
 constexpr int kRopeSplitMaxWidth = 12288;
 hipError_t launch_rope_kv(int dtype, int R, int Hq, int Hkv, int hd, float theta, const float* qkv,
                           const int32_t* pos, const int32_t* slot, void* q, void* kpool,
-                          void* vpool, hipStream_t st, bool rot_tiled = false, int splits = 0);
+                          void* vpool, hipStream_t st, bool rot_tiled = false, int splits = 0,
+                          const float2* ang = nullptr);
 
 // Zero the K and V entries of `n` flat slots (device list) in every layer of
 // a pool whose layer l holds K at kv + l * layer_stride and V at + v_off

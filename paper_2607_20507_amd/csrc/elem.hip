@@ -53,13 +53,28 @@ __global__ __launch_bounds__(256) void upload_mapped_kernel(const uint32_t* __re
   }
 }
 
+// The rotation angles of one row, by the last threads of the workgroup.  Once
+// per forward: evaluated by every layer's QKV epilogue and rope_kv, the fp64
+// arithmetic was @ROT@
+__device__ __forceinline__ void row_angles(const RotTable& rot, int r) {
+  if (!rot.ang) return;
+  const int half = rot.hd / 2;
+  for (int i = static_cast<int>(blockDim.x) - 1 - static_cast<int>(threadIdx.x); i < half; i += blockDim.x) {
+    double sn, cs;
+    sincos(static_cast<double>(rot.pos[r]) * exp(-(2.0 * i / rot.hd) * log(static_cast<double>(rot.theta))), &sn, &cs);
+    rot.ang[static_cast<size_t>(r) * half + i] = make_float2(static_cast<float>(cs), static_cast<float>(sn));
+  }
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void embed_kernel(int d, const int32_t* __restrict__ tok_src,
                                                     const int32_t* __restrict__ tok_pool,
                                                     const T* __restrict__ E, float* __restrict__ h,
                                                     int32_t* __restrict__ row_tok, T* __restrict__ hb,
-                                                    const T* __restrict__ wn, float* __restrict__ ss) {
+                                                    const T* __restrict__ wn, float* __restrict__ ss,
+                                                    const RotTable rot) {
   const int r = blockIdx.x;
+  row_angles(rot, r);
   const int s = tok_src[r];
   const int tok = s >= 0 ? s : tok_pool[-1 - s];
   if (threadIdx.x == 0) row_tok[r] = tok;
@@ -118,7 +133,8 @@ __global__ __launch_bounds__(256) void embed_vec_kernel(int d, const int32_t* __
                                                         const int32_t* __restrict__ tok_pool,
                                                         const T* __restrict__ E, float* __restrict__ h,
                                                         int32_t* __restrict__ row_tok, T* __restrict__ hb,
-                                                        const T* __restrict__ wn, float* __restrict__ ss) {
+                                                        const T* __restrict__ wn, float* __restrict__ ss,
+                                                        const RotTable rot) {
   const int r = blockIdx.x;
   const int s = tok_src[r];
   const int tok = s >= 0 ? s : tok_pool[-1 - s];
@@ -132,6 +148,7 @@ __global__ __launch_bounds__(256) void embed_vec_kernel(int d, const int32_t* __
     load8(e + 8 * j, x[c]);
     if (hb) load8(wn + 8 * j, w[c]);
   }
+  row_angles(rot, r);  // while the loads are in flight
   float* o = h + static_cast<size_t>(r) * d;
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
@@ -239,7 +256,7 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(int Hq, int Hkv, int hd, f
                                                       const int32_t* __restrict__ slot,
                                                       T* __restrict__ q, T* __restrict__ kpool,
                                                       T* __restrict__ vpool, bool rot_tiled, int S,
-                                                      size_t sstride) {
+                                                      size_t sstride, const float2* __restrict__ ang) {
   const int r = blockIdx.x;
   const int half = hd / 2;
   const int width = (Hq + 2 * Hkv) * hd;
@@ -282,18 +299,21 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(int Hq, int Hkv, int hd, f
     xk = xq + nqc;
     xv = xk + nkc;
   }
-  const double p = static_cast<double>(pos[r]);
   const int sl = slot[r];
   const int page = sl >> 4, off = sl & 15;
-  const double lt = log(static_cast<double>(theta));
   // the row's rotation angles (they depend on the pair index only, not on
-  // the head), once per workgroup in fp64, by the last hd / 2 threads (with
-  // the split, while the first ones wait for the partials)
+  // the head): from the forward's table, else once per workgroup in fp64, by
+  // the last hd / 2 threads (with the split, while the first ones wait for
+  // the partials)
   __shared__ float s_cos[kRopeMaxHalf], s_sin[kRopeMaxHalf];
   const int ai = static_cast<int>(threadIdx.x) - (static_cast<int>(blockDim.x) - half);
-  if (ai >= 0) {
+  if (ai >= 0 && ang) {
+    const float2 v = ang[static_cast<size_t>(r) * half + ai];
+    s_cos[ai] = v.x;
+    s_sin[ai] = v.y;
+  } else if (ai >= 0) {
     double sn, cs;
-    sincos(p * exp(-(2.0 * ai / hd) * lt), &sn, &cs);
+    sincos(static_cast<double>(pos[r]) * exp(-(2.0 * ai / hd) * log(static_cast<double>(theta))), &sn, &cs);
     s_cos[ai] = static_cast<float>(cs);
     s_sin[ai] = static_cast<float>(sn);
   }
@@ -421,7 +441,7 @@ hipError_t launch_kv_move(int dtype, const KvMoveJob& j, hipStream_t st) {
 
 hipError_t launch_embed(int dtype, int R, int d, const int32_t* tok_src, const int32_t* tok_pool,
                         const void* E, float* h, int32_t* row_tok, hipStream_t st, void* hb, const void* wn,
-                        float* ss) {
+                        float* ss, const RotTable& rot) {
   if (R <= 0) return hipSuccess;
   if (ss && d % 16 != 0) return hipErrorInvalidValue;
   const auto aligned = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
@@ -431,21 +451,21 @@ hipError_t launch_embed(int dtype, int R, int d, const int32_t* tok_src, const i
       auto* k = nch == 1 ? embed_vec_kernel<float, 1> : nch == 2 ? embed_vec_kernel<float, 2>
               : nch == 3 ? embed_vec_kernel<float, 3> : embed_vec_kernel<float, 4>;
       k<<<R, 256, 0, st>>>(d, tok_src, tok_pool, static_cast<const float*>(E), h, row_tok,
-                           static_cast<float*>(hb), static_cast<const float*>(wn), ss);
+                           static_cast<float*>(hb), static_cast<const float*>(wn), ss, rot);
     } else {
       auto* k = nch == 1 ? embed_vec_kernel<bf16_t, 1> : nch == 2 ? embed_vec_kernel<bf16_t, 2>
               : nch == 3 ? embed_vec_kernel<bf16_t, 3> : embed_vec_kernel<bf16_t, 4>;
       k<<<R, 256, 0, st>>>(d, tok_src, tok_pool, static_cast<const bf16_t*>(E), h, row_tok,
-                           static_cast<bf16_t*>(hb), static_cast<const bf16_t*>(wn), ss);
+                           static_cast<bf16_t*>(hb), static_cast<const bf16_t*>(wn), ss, rot);
     }
     return hipGetLastError();
   }
   if (dtype == 0)
     embed_kernel<float><<<R, 256, 0, st>>>(d, tok_src, tok_pool, static_cast<const float*>(E), h, row_tok,
-                                           static_cast<float*>(hb), static_cast<const float*>(wn), ss);
+                                           static_cast<float*>(hb), static_cast<const float*>(wn), ss, rot);
   else
     embed_kernel<bf16_t><<<R, 256, 0, st>>>(d, tok_src, tok_pool, static_cast<const bf16_t*>(E), h, row_tok,
-                                            static_cast<bf16_t*>(hb), static_cast<const bf16_t*>(wn), ss);
+                                            static_cast<bf16_t*>(hb), static_cast<const bf16_t*>(wn), ss, rot);
   return hipGetLastError();
 }
 
@@ -463,7 +483,7 @@ hipError_t launch_rmsnorm(int dtype, int R, int d, const float* h, const int32_t
 
 hipError_t launch_rope_kv(int dtype, int R, int Hq, int Hkv, int hd, float theta, const float* qkv,
                           const int32_t* pos, const int32_t* slot, void* q, void* kpool,
-                          void* vpool, hipStream_t st, bool rot_tiled, int splits) {
+                          void* vpool, hipStream_t st, bool rot_tiled, int splits, const float2* ang) {
   if (R <= 0) return hipSuccess;
   if (hd % 2 != 0 || hd > 2 * kRopeMaxHalf || (rot_tiled && hd % 16 != 0)) return hipErrorInvalidValue;
   if (Hkv <= 0 || Hq % Hkv != 0) return hipErrorInvalidValue;
@@ -476,19 +496,19 @@ hipError_t launch_rope_kv(int dtype, int R, int Hq, int Hkv, int hd, float theta
   if (dtype == 0 && splits > 0)
     rope_kv_kernel<float, true><<<grid, 256, lds, st>>>(Hq, Hkv, hd, theta, qkv, pos, slot, static_cast<float*>(q),
                                                    static_cast<float*>(kpool), static_cast<float*>(vpool),
-                                                   rot_tiled, splits, sstride);
+                                                   rot_tiled, splits, sstride, ang);
   else if (dtype == 0)
     rope_kv_kernel<float, false><<<grid, 256, 0, st>>>(Hq, Hkv, hd, theta, qkv, pos, slot, static_cast<float*>(q),
                                                     static_cast<float*>(kpool), static_cast<float*>(vpool),
-                                                    rot_tiled, 0, 0);
+                                                    rot_tiled, 0, 0, ang);
   else if (splits > 0)
     rope_kv_kernel<bf16_t, true><<<grid, 256, lds, st>>>(Hq, Hkv, hd, theta, qkv, pos, slot, static_cast<bf16_t*>(q),
                                                     static_cast<bf16_t*>(kpool), static_cast<bf16_t*>(vpool),
-                                                    rot_tiled, splits, sstride);
+                                                    rot_tiled, splits, sstride, ang);
   else
     rope_kv_kernel<bf16_t, false><<<grid, 256, 0, st>>>(Hq, Hkv, hd, theta, qkv, pos, slot, static_cast<bf16_t*>(q),
                                                      static_cast<bf16_t*>(kpool), static_cast<bf16_t*>(vpool),
-                                                     rot_tiled, 0, 0);
+                                                     rot_tiled, 0, 0, ang);
   return hipGetLastError();
 }
 

@@ -14,7 +14,7 @@ enum GemmEpi {
   kEpiQKVRope = 3    // fused path only: RoPE on q and k, q out, k and v into the paged cache
 };
 
-// Extras of the fused skinny GEMM (bf16, R <= 16), which folds the RMSNorm
+// Extras of the fused skinny GEMM (bf16, few rows), which folds the RMSNorm
 // and the RoPE / KV append of the decoder into the GEMMs around them.
 struct GemmFuse {
   // Consumer side of RMSNorm: X holds rows bf16(h (.) w) written by the
@@ -30,19 +30,19 @@ struct GemmFuse {
   const void* wn = nullptr;
   float* ss_out = nullptr;
   // kEpiQKVRope: W is the [(Hq + 2 Hkv) hd, K] QKV projection; rotate-half
-  // RoPE (angle pos[m] * theta^(-2i/hd), evaluated in fp64) on the q and k
-  // heads; q to qout [R][Hq][hd], k and v to K [page][Hkv][16][hd] and
+  // RoPE (ang[m][i]: cos and sin of row m's pair i, launch_embed) on the q and
+  // k heads; q to qout [R][Hq][hd], k and v to K [page][Hkv][16][hd] and
   // V^T [page][Hkv][hd][16] at slot[m] = page * 16 + offset.
   int Hq = 0, Hkv = 0, hd = 0;
-  float theta = 0.f;
-  const int32_t* pos = nullptr;
+  const float2* ang = nullptr;
   const int32_t* slot = nullptr;
   void* qout = nullptr;
   void* kpool = nullptr;
   void* vpool = nullptr;
 };
 
-// Fused skinny GEMM (bf16, R <= 16, K % 128 == 0); epi as above.
+// Fused skinny GEMM (bf16, R <= kFusedMaxRows, K % 128 == 0); epi as above.
+constexpr int kFusedMaxRows = 64;
 hipError_t launch_gemm_fused(int R, int N, int K, const void* X, const void* W, void* Y, int epi,
                              const GemmFuse& f, hipStream_t st, const int32_t* row_map = nullptr);
 

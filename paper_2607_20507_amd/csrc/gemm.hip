@@ -116,44 +116,61 @@ __device__ __forceinline__ int qkv_tile_row(const GemmFuse& f, int tile, int l16
   return *head * f.hd + *dim;
 }
 
-// 1 / rms of each X row (R <= 16) from the producer's sums of squares per 8
-// columns, into s_rs.  Wave w takes rows w, w + waves, ...; lane l sums
-// entries l, l + 64, ... of the row, eight loads issued together per round,
-// then a fixed-order shuffle tree.  Run by the whole workgroup.
-__device__ __forceinline__ void row_rscale(const GemmFuse& fu, int R, int K, float* s_rs) {
+// 1 / rms of the X rows m0 .. min(m0 + rows, R) - 1 from the producer's sums
+// of squares per 8 columns, into s_rs.  Wave w takes rows w, w + waves, ...,
+// RW of them at a time; lane l sums entries l, l + 64, ... of the row, eight
+// loads of each row issued together per round, then a fixed-order shuffle tree.
+// Run by the whole workgroup.
+template <int RW>
+__device__ __forceinline__ void row_rscale(const GemmFuse& fu, int R, int K, float* s_rs, int m0, int rows) {
   const int np = K / 8;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
-  for (int rr = wave; rr < R; rr += nw) {
-    const float* sp = fu.ss + static_cast<size_t>(fu.xrow ? fu.xrow[rr] : rr) * np;
-    float a = 0.f;
+  const int n = min(R - m0, rows);
+  for (int r0 = wave; r0 < n; r0 += RW * nw) {
+    const float* sp[RW];
+    float a[RW];
+#pragma unroll
+    for (int i = 0; i < RW; ++i) {
+      const int m = m0 + min(r0 + i * nw, n - 1);
+      sp[i] = fu.ss + static_cast<size_t>(fu.xrow ? fu.xrow[m] : m) * np;
+      a[i] = 0.f;
+    }
     for (int p0 = 0; p0 < np; p0 += 8 * kWave) {
-      float v[8];
+      float v[RW][8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int p = p0 + j * kWave + lane;
-        v[j] = p < np ? sp[p] : 0.f;
-      }
+      for (int i = 0; i < RW; ++i)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) a += v[j];
+        for (int j = 0; j < 8; ++j) {
+          const int p = p0 + j * kWave + lane;
+          v[i][j] = p < np ? sp[i][p] : 0.f;
+        }
+#pragma unroll
+      for (int i = 0; i < RW; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) a[i] += v[i][j];
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, kWave);
-    if (lane == 0) s_rs[rr] = 1.f / sqrtf(a / static_cast<float>(K) + fu.eps);
+    for (int i = 0; i < RW; ++i) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) a[i] += __shfl_xor(a[i], o, kWave);
+      if (lane == 0 && r0 + i * nw < n) s_rs[r0 + i * nw] = 1.f / sqrtf(a[i] / static_cast<float>(K) + fu.eps);
+    }
   }
 }
 
 // Operands of the fused epilogue that do not depend on the GEMM result, read
 // before the main loop so that their latency hides under the weight stream:
-// the residual and norm weight (kEpiAddF32), the slot and position
+// the residual and norm weight (kEpiAddF32), the slot and rotation
 // (kEpiQKVRope).
 struct EpiPre {
   float h = 0.f, wn = 0.f;
-  int slot = 0, pos = 0;
+  int slot = 0;
+  float2 rot = {1.f, 0.f};
 };
 
 template <int EPI>
 __device__ __forceinline__ EpiPre epi_prefetch(const GemmFuse& fu, int m, int l16, int tile, int R, int N,
-                                               const void* __restrict__ Y) {
+                                               const void* __restrict__ Y, int qk_tiles) {
   EpiPre p;
   const int n = tile * 16 + l16;
   if (m >= R) return p;
@@ -162,15 +179,19 @@ __device__ __forceinline__ EpiPre epi_prefetch(const GemmFuse& fu, int m, int l1
     if (fu.hb) p.wn = bf16_to_f32(static_cast<const bf16_t*>(fu.wn)[n]);
   } else if (EPI == kEpiQKVRope) {
     p.slot = fu.slot[m];
-    p.pos = fu.pos[m];
+    if (tile < qk_tiles) {
+      int head, dim;
+      qkv_tile_row(fu, tile, l16, &head, &dim);
+      p.rot = fu.ang[static_cast<size_t>(m) * (fu.hd / 2) + dim % (fu.hd / 2)];
+    }
   }
   return p;
 }
 
-// Epilogue of the fused GEMMs for output row m (< 16) and tile column l16 of
+// Epilogue of the fused GEMMs for output row m and tile column l16 of
 // 16-feature tile `tile`, given the (row-scaled) dot products v (and vu,
 // the up rows of SwiGLU) and the prefetched operands.  Run by whole waves:
-// threads 0..255 with m = 4 (lane / 16) + r, so the 16 lanes of a group hold
+// threads 0..255 with m % 16 = 4 (lane / 16) + r, so the 16 lanes of a group hold
 // the 16 columns of a row and exchange values with shuffles.
 template <int EPI>
 __device__ __forceinline__ void fused_epilogue(const GemmFuse& fu, const EpiPre& p, int m, int l16, int tile,
@@ -202,11 +223,7 @@ __device__ __forceinline__ void fused_epilogue(const GemmFuse& fu, const EpiPre&
       if (tile < qk_tiles) {
         int head, dim;
         qkv_tile_row(fu, tile, l16, &head, &dim);
-        const int i = dim % (fu.hd / 2);
-        double sn, cs;
-        sincos(static_cast<double>(p.pos) * exp(-(2.0 * i / fu.hd) * log(static_cast<double>(fu.theta))), &sn,
-               &cs);
-        const float c = static_cast<float>(cs), sv = static_cast<float>(sn);
+        const float c = p.rot.x, sv = p.rot.y;
         // first half: a cos - b sin; second half: b cos + a sin (a, b = pair)
         const float o = (l16 < 8) ? v * c - partner * sv : v * c + partner * sv;
         if (head < fu.Hq)
@@ -236,16 +253,21 @@ __global__ __launch_bounds__(kSkinnyMaxWaves * kWave) void gemm_skinny_bf16(
   constexpr bool QKV = (EPI == kEpiQKVRope);
   constexpr int NS = SW ? 2 : 1;  // weight streams: gate and up tiles for SwiGLU
   constexpr int NACC = MT * NS;
-  static_assert(!FUSE || MT == 1, "the fused path covers up to 16 rows");
+  static_assert(!FUSE || MT == 1, "the fused path takes 16 rows per workgroup");
   static_assert(FUSE || !QKV, "the QKV epilogue is fused only");
   extern __shared__ float red[];  // [waves][NACC][4][64]
-  __shared__ float s_rs[16];
+  __shared__ float s_rs[16 * MT];
 
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
   const int nw = blockDim.x / kWave;
   const int row = lane & 15, g = lane >> 4;
-  const int tile = blockIdx.x;
+  // several row blocks (fused path): those of a tile 8 workgroups apart, so
+  // that they run on one XCD and its L2 takes W from HBM once
+  const int nrb = FUSE ? (R + 15) / 16 : 1, tiles = (N + 15) / 16;
+  const int tile = nrb == 1 ? blockIdx.x : blockIdx.x / (8 * nrb) * 8 + blockIdx.x % 8;
+  const int m0 = nrb == 1 ? 0 : blockIdx.x / 8 % nrb * 16;
+  if (tile >= tiles) return;
   const int qk_tiles = QKV ? (fu.Hq + fu.Hkv) * fu.hd / 16 : 0;
   // Step s of lane group g reads row 4 s + g of the tile at chunk position
   // `row` (tiled layout): 16 bytes of W[tile * 16 + row][32 s + 8 g ..].  A
@@ -265,18 +287,17 @@ __global__ __launch_bounds__(kSkinnyMaxWaves * kWave) void gemm_skinny_bf16(
   bool xv[MT];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
-    const int m = mt * 16 + row;
+    const int m = m0 + mt * 16 + row;
     xv[mt] = m < R;
     const int src = !xv[mt] ? 0 : ((FUSE && fu.xrow) ? fu.xrow[m] : m);
     xr[mt] = X + static_cast<size_t>(src) * K + g * 8;
   }
   // (measured: before the main loop here, after it in the GEMV)
-  if (FUSE && fu.ss) row_rscale(fu, R, K, s_rs);
+  if (FUSE && fu.ss) row_rscale<2>(fu, R, K, s_rs, m0, 16);
   // the fused epilogue (MT = 1) is run by threads 0..255, one element each
   EpiPre pre;
-  const int e_r = (threadIdx.x / kWave) & 3;
-  const int e_m = 4 * (lane >> 4) + e_r, e_l16 = lane & 15;
-  if (FUSE && threadIdx.x < 256) pre = epi_prefetch<EPI>(fu, e_m, e_l16, tile, R, N, Y);
+  const int e_m = m0 + 4 * (lane >> 4) + ((threadIdx.x / kWave) & 3);
+  if (FUSE && threadIdx.x < 256) pre = epi_prefetch<EPI>(fu, e_m, row, tile, R, N, Y, qk_tiles);
   f32x4 acc[MT][NS];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
@@ -327,7 +348,7 @@ __global__ __launch_bounds__(kSkinnyMaxWaves * kWave) void gemm_skinny_bf16(
   // exchanges need.
   for (int e = threadIdx.x; e < MT * 256; e += blockDim.x) {
     const int mt = e / 256, r = (e / kWave) & 3, ln = e & (kWave - 1);
-    const int m = mt * 16 + 4 * (ln >> 4) + r, l16 = ln & 15;
+    const int m = m0 + mt * 16 + 4 * (ln >> 4) + r, l16 = ln & 15;
     float v = 0.f, vu = 0.f;
     for (int wv = 0; wv < nw; ++wv) {
       v += red[((wv * NACC + mt * NS) * 4 + r) * kWave + ln];
@@ -335,7 +356,7 @@ __global__ __launch_bounds__(kSkinnyMaxWaves * kWave) void gemm_skinny_bf16(
     }
     if (FUSE) {
       if (fu.ss) {
-        const float rs = s_rs[m];
+        const float rs = s_rs[m - m0];
         v *= rs;
         vu *= rs;
       }
@@ -429,7 +450,7 @@ __global__ __launch_bounds__(512) void gemv_bf16(const bf16_t* __restrict__ X, c
   // threads 0..255 run the epilogue: output row m = 4 (lane / 16) + (wave % 4)
   const int em = 4 * (lane >> 4) + (wave & 3);
   EpiPre pre;
-  if (threadIdx.x < 256) pre = epi_prefetch<EPI>(fu, em, lane & 15, tile, R, N, Y);
+  if (threadIdx.x < 256) pre = epi_prefetch<EPI>(fu, em, lane & 15, tile, R, N, Y, qk_tiles);
   const int nb = K / 128;
   const int per = (nb + ngw - 1) / ngw;
   const int kb0 = gw * per, kb1 = min(nb, kb0 + per);
@@ -459,7 +480,7 @@ __global__ __launch_bounds__(512) void gemv_bf16(const bf16_t* __restrict__ X, c
           if (m < R) a[m] += dot8(w[b][q], x[b][m][q]);
     }
   }
-  if (fu.ss) row_rscale(fu, R, K, s_rs);
+  if (fu.ss) row_rscale<1>(fu, R, K, s_rs, 0, RM);
 #pragma unroll
   for (int m = 0; m < RM; ++m) {
     if (HALF) a[m] += __shfl_xor(a[m], 8, kWave);
@@ -1644,7 +1665,9 @@ hipError_t skinny(int R, int N, int K, const void* X, const void* W, void* Y, hi
   if (FUSE && nw < 4) return hipErrorInvalidValue;  // the fused epilogue needs 256 threads
   const int kbpw = (nb + nw - 1) / nw;
   const size_t lds = static_cast<size_t>(nw) * NACC * 256 * sizeof(float);
-  launch_kernel(gemm_skinny_bf16<MT, EPI, FUSE>, dim3(tiles), dim3(nw * kWave), lds, st, static_cast<const bf16_t*>(X),
+  const int nrb = FUSE ? (R + 15) / 16 : 1;  // (several: whole groups of 8 tiles per row block)
+  const int grid = nrb == 1 ? tiles : (tiles + 7) / 8 * 8 * nrb;
+  launch_kernel(gemm_skinny_bf16<MT, EPI, FUSE>, dim3(grid), dim3(nw * kWave), lds, st, static_cast<const bf16_t*>(X),
                 static_cast<const bf16_t*>(W), Y, R, N, K, kbpw, row_map, fu);
   return hipGetLastError();
 }
@@ -2046,7 +2069,7 @@ size_t gemm_splitk_bytes(int R_max, int Nw_max) {
 hipError_t launch_gemm_fused(int R, int N, int K, const void* X, const void* W, void* Y, int epi,
                              const GemmFuse& f, hipStream_t st, const int32_t* row_map) {
   if (R <= 0 || N <= 0) return hipSuccess;
-  if (R > 16 || K % 128 != 0 || N % 16 != 0) return hipErrorInvalidValue;
+  if (R > kFusedMaxRows || K % 128 != 0 || N % 16 != 0) return hipErrorInvalidValue;
   if (epi == kEpiQKVRope && (f.hd % 16 != 0 || N != (f.Hq + 2 * f.Hkv) * f.hd)) return hipErrorInvalidValue;
   if (R <= kGemvRows && !gemv_lm_skinny(R, N, K, epi)) {
     switch (epi) {
