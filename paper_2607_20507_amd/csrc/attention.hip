@@ -349,15 +349,22 @@ __global__ __launch_bounds__(64 * W, NT <= 2 ? 2 : 1) void attn_tree_bf16_kernel
 
 // ---------------------------------------------------------------------------
 // Causal prefill: long runs of consecutive rows of one sequence.  One
-// workgroup of 8 waves (two per SIMD, so that one wave's softmax arithmetic
-// overlaps the other's MFMAs) per (block of 256 / G rows, kv head): its 256
-// query vectors (rows x the G query heads of the kv head) share every K / V
-// load.  The keys 0 .. last row's position are brought into LDS 64 at a time
-// (four pages of K and of V, three stage buffers, two stages in flight) by
-// direct-to-LDS loads of whole page blocks, and each wave runs both products
-// for its own 32 query vectors (2 tiles) from there, with the key permutation
-// and lane-local softmax of attn_bf16_body.  Each wave sees every key of its
-// rows, so it normalises its own output: no key splits, no combine.
+// workgroup of 8 waves (two per SIMD) per (block of 256 / G rows, kv head):
+// its 256 query vectors (rows x the G query heads of the kv head) share every
+// K / V load.  The keys 0 .. last row's position are brought into LDS 64 at a
+// time (four pages of K and of V, three stage buffers) by direct-to-LDS loads
+// of whole page blocks, and each wave runs both products for its own 32 query
+// vectors (2 tiles) from there, with the key permutation and lane-local
+// softmax of attn_bf16_body.  Each wave sees every key of its rows, so it
+// normalises its own output: no key splits, no combine.
+// A 32-key chunk is a matrix phase (its scores, the output update of the chunk
+// before) and a vector phase (its softmax), a barrier after each, and waves
+// 4..7 run one phase behind waves 0..3, with which they share the SIMDs: one
+// of a SIMD's two waves multiplies while the other takes its exponentials.
+// Measured by cycle counters: a phase pair costs about what the SIMD's MFMAs
+// (512 cycles) and vector instructions (560) add up to, so the softmax is kept
+// short: 8192 rows (32q / 8kv, head dim 128) 559 -> 490 us (970 -> 1120
+// TFLOP/s), 2048 rows 89 -> 69 us, head dim 64 at 4096 rows 127 -> 114 us.
 // The running maximum of a query vector is raised only when a score exceeds
 // it by more than 2^8 (scores are base-2 logits): each lane compares its own
 // 8 scores against it, and only when some lane of the wave finds a larger
@@ -404,8 +411,9 @@ __global__ __launch_bounds__(512, 1) void attn_prefill_bf16_kernel(AttnArgs a, c
   static_assert(LPW * 64 == BU && NW == 8, "one page block per wave and stage");
   const bool wv = wave >= 4;
   const int wpg = wave & 3;
-  auto issue = [&](int j, int b) {
-    const int page = __builtin_amdgcn_readfirstlane(s_pt[min(4 * j + wpg, np - 1)]);
+  auto page_of = [&](int j) { return s_pt[min(4 * j + wpg, np - 1)]; };
+  auto issue = [&](int page_id, int b) {
+    const int page = __builtin_amdgcn_readfirstlane(page_id);
     const bf16_t* blk = (wv ? vp : kp) + static_cast<size_t>(page * a.Hkv + gkv) * 16 * HD;
     const uint32_t dst = lds_addr(wv ? &sv[b][wpg * BU] : &sk[b][wpg * BU]);
 #pragma unroll
@@ -434,133 +442,175 @@ __global__ __launch_bounds__(512, 1) void attn_prefill_bf16_kernel(AttnArgs a, c
   const int pos_lo = it.pos0 + (32 * wave) / G;
   const int pos_hi = it.pos0 + min((32 * wave + 31) / G, it.nrows - 1);
   const float scale = kLog2e / sqrtf(static_cast<float>(HD));
-  float mrun[NT], lrun[NT];
+  // minus the running maximum (base-2 logits; -inf: no key yet, every p is 0),
+  // the raw score above which it is raised, two partial sums of p
+  float mneg[NT], mlim[NT], lrun[NT][2];
   f32x4 acc[DT][NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    mrun[nt] = -INFINITY;
-    lrun[nt] = 0.f;
+    mneg[nt] = mlim[nt] = -INFINITY;
+    lrun[nt][0] = lrun[nt][1] = 0.f;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) acc[dt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
-  // one 32-key chunk (keys c0 .., pages 2 h, 2 h + 1 of buffer b)
-  // K and V^T operands of chunk h of buffer b, read from LDS
-  auto read_k = [&](int b, int h, uint4 (&kf)[2][DS]) {
+  // K and V^T operands of 32-key chunk h of buffer b, read from LDS
+  uint4 kf[2][DS], vf[DT];
+  auto read_k = [&](int b, int h) {
     const uint4* kb = &sk[b][(2 * h + (l16 >> 3)) * BU];
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
       for (int s = 0; s < DS; ++s) kf[hh][s] = kb[((s * 2 + hh) * 4 + g) * 8 + (l16 & 7)];
   };
-  auto read_v = [&](int b, int h, uint4 (&vf)[DT]) {
+  // (quarter q of V^T's tiles)
+  auto read_v = [&](int b, int h, int q) {
     const uint4* vb = &sv[b][(2 * h + (g >> 1)) * BU];
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) vf[dt] = vb[(dt * 2 + (g & 1)) * 16 + l16];
+    for (int dt = q * DT / 4; dt < (q + 1) * DT / 4; ++dt) vf[dt] = vb[(dt * 2 + (g & 1)) * 16 + l16];
   };
-  auto chunk = [&](int c0, const uint4 (&kf)[2][DS], const uint4 (&vf)[DT]) {
-    // every key at or below every row of the wave and inside the sequence
-    const bool full = c0 + 31 <= pos_lo && c0 + 31 < t1;
-    uint4 pf[NT];
+  f32x4 sc[NT][2];
+  uint4 pf[NT];
+  // scores of the chunk in kf
+  auto scores = [&] {
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      f32x4 s0 = f32x4{0.f, 0.f, 0.f, 0.f}, s1 = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int nt = 0; nt < NT; ++nt) sc[nt][0] = sc[nt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int s = 0; s < DS; ++s) {
-        s0 = mfma16x16x32(kf[0][s], qf[nt][s], s0);
-        s1 = mfma16x16x32(kf[1][s], qf[nt][s], s1);
+    for (int s = 0; s < DS; ++s)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) sc[nt][hh] = mfma16x16x32(kf[hh][s], qf[nt][s], sc[nt][hh]);
+  };
+  // output update with the chunk of keys c0 .. in vf and its probabilities in pf
+  auto output = [&](int c0) {
+    if (c0 + 32 > t1) {
+      // keys past the sequence hold stale or uninitialised V (their
+      // probabilities are 0, but 0 x NaN is not)
+      asm volatile("");
+      const int nvalid = min(max(t1 - (c0 + 8 * g), 0), 8);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        vf[dt].x = mask_pair(vf[dt].x, nvalid);
+        vf[dt].y = mask_pair(vf[dt].y, nvalid - 2);
+        vf[dt].z = mask_pair(vf[dt].z, nvalid - 4);
+        vf[dt].w = mask_pair(vf[dt].w, nvalid - 6);
       }
-      float raw[8];  // raw scores, -inf where masked
-#pragma unroll
-      for (int j = 0; j < 8; ++j) raw[j] = (j < 4) ? s0[j] : s1[j - 4];
-      if (!full) {
-        asm volatile("");  // keeps the mask a branch around diagonal chunks (not selects everywhere)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) raw[j] = (c0 + 8 * g + j <= klim[nt]) ? raw[j] : -INFINITY;
-      }
-      float mx = raw[0];
-#pragma unroll
-      for (int j = 1; j < 8; ++j) mx = fmaxf(mx, raw[j]);
-      mx *= scale;  // base-2 logit (scale > 0)
-      if (__any(mx > mrun[nt] + kPrefillRescaleLog2)) {
-        // the query vector's maximum over the chunk, from all lanes holding it
-        mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-        const bool grow = mx > mrun[nt] + kPrefillRescaleLog2;
-        const float alpha = grow ? ((mrun[nt] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mrun[nt] - mx)) : 1.f;
-        if (grow) mrun[nt] = mx;
-        lrun[nt] *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) acc[dt][nt] *= alpha;
-      }
-      // p = 2^(raw scale - m): one FMA per score; with no maximum yet (no key
-      // of the query vector so far) every p is 0
-      const float mneg = (mrun[nt] == -INFINITY) ? -INFINITY : -mrun[nt];
-      float p[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) p[j] = __builtin_amdgcn_exp2f(fmaf(raw[j], scale, mneg));
-      float ps = 0.f;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) ps += p[j];
-      lrun[nt] += ps;
-      pf[nt] = make_uint4(cvt_pk_bf16(p[0], p[1]), cvt_pk_bf16(p[2], p[3]), cvt_pk_bf16(p[4], p[5]),
-                          cvt_pk_bf16(p[6], p[7]));
     }
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) acc[dt][nt] = mfma16x16x32(vf[dt], pf[nt], acc[dt][nt]);
   };
-
-  issue(0, 0);
-  if (ns > 1) issue(1, 1);
-  for (int j = 0; j < ns; ++j) {
-    // stage j has landed (stage j + 1 may still be in flight), every wave is
-    // done with stage j - 1, whose buffer stage j + 2 now fills
-    if (j + 1 < ns) {
-      SPEC_WAIT_VM_LDS(LPW);
-    } else {
-      SPEC_WAIT_VM_LDS(0);
+  // probabilities of the chunk of keys c0 .. from its scores, with the reads
+  // of the chunk's V^T (chunk h of buffer b) between them: issued together
+  // they held the wave at the LDS pipe before its arithmetic could start.
+  // Both query tiles go through each branch together: taken branches cost more
+  // than the few instructions they skip.
+  auto softmax = [&](int c0, int b, int h) {
+    read_v(b, h, 0);
+    read_v(b, h, 1);
+    // some key above a row of the wave or past the sequence
+    if (c0 + 31 > pos_lo || c0 + 31 >= t1) {
+      asm volatile("");  // keeps the mask a branch around diagonal chunks (not selects everywhere)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (c0 + 8 * g + j > klim[nt]) sc[nt][j / 4][j % 4] = -INFINITY;
     }
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_barrier();
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    if (j + 2 < ns) issue(j + 2, (j + 2) % NB);
-    const int b = j % NB;
-    if (j == ns - 1 && t1 < 64 * ns) {
-      // keys past the sequence in the last stage hold stale or uninitialised
-      // V (their probabilities are 0, but 0 x NaN is not): zero them in LDS.
-      // Unit ((d / 16) 2 + k / 8) 16 + d % 16 of a page block holds keys
-      // 8 (k / 8) .. + 7 of dim d.
-      for (int u = threadIdx.x; u < SU; u += 64 * NW) {
-        const int k0 = 64 * j + (u / BU) * 16 + ((u % BU) / 16 % 2) * 8;
-        const int keep = min(max(t1 - k0, 0), 8);
-        if (keep < 8) {
-          uint4 v = sv[b][u];
-          v.x = mask_pair(v.x, keep);
-          v.y = mask_pair(v.y, keep - 2);
-          v.z = mask_pair(v.z, keep - 4);
-          v.w = mask_pair(v.w, keep - 6);
-          sv[b][u] = v;
+    float mx[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      mx[nt] = sc[nt][0][0];
+#pragma unroll
+      for (int j = 1; j < 8; ++j) mx[nt] = fmaxf(mx[nt], sc[nt][j / 4][j % 4]);
+    }
+    static_assert(NT == 2, "one test for both tiles");
+    if (__any(mx[0] > mlim[0] || mx[1] > mlim[1])) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        // the query vector's maximum over the chunk, from all lanes holding it
+        float m = mx[nt];
+        m = fmaxf(m, __shfl_xor(m, 16, kWave));
+        m = fmaxf(m, __shfl_xor(m, 32, kWave));
+        if (m > mlim[nt]) {
+          const float mb = m * scale;  // base-2 logit (scale > 0)
+          const float alpha = mneg[nt] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(-mneg[nt] - mb);
+          mneg[nt] = -mb;
+          mlim[nt] = m + kPrefillRescaleLog2 / scale;
+#pragma unroll
+          for (int i = 0; i < 2; ++i) lrun[nt][i] *= alpha;
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) acc[dt][nt] *= alpha;
         }
       }
-      __syncthreads();
     }
-    // the first chunk's operands and the second's K read up front, so that
-    // their LDS latency hides under the first chunk's arithmetic (the
-    // second's V^T after it: registers)
-    uint4 kf0[2][DS], vf0[DT], kf1[2][DS], vf1[DT];
-    read_k(b, 0, kf0);
-    read_v(b, 0, vf0);
-    read_k(b, 1, kf1);
-    if (64 * j <= pos_hi) chunk(64 * j, kf0, vf0);  // else above every row of this wave
-    read_v(b, 1, vf1);
-    if (64 * j + 32 <= pos_hi) chunk(64 * j + 32, kf1, vf1);
+    read_v(b, h, 2);
+    read_v(b, h, 3);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      // p = 2^(raw scale - m): one FMA per score
+      float p[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) p[j] = __builtin_amdgcn_exp2f(fmaf(sc[nt][j / 4][j % 4], scale, mneg[nt]));
+#pragma unroll
+      for (int j = 0; j < 8; ++j) lrun[nt][j % 2] += p[j];
+      pf[nt] = make_uint4(cvt_pk_bf16(p[0], p[1]), cvt_pk_bf16(p[2], p[3]), cvt_pk_bf16(p[4], p[5]),
+                          cvt_pk_bf16(p[6], p[7]));
+    }
+  };
+  auto phase_end = [&] {
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  };
+
+  issue(page_of(0), 0);
+  if (ns > 1) {
+    issue(page_of(1), 1);
+    SPEC_WAIT_VM_LDS(LPW);
+  } else {
+    SPEC_WAIT_VM_LDS(0);
   }
+  int page_next = page_of(2);
+  phase_end();  // stage 0 has landed
+  read_k(0, 0);
+  if (wave >= 4) phase_end();  // waves 4..7 run one phase behind
+  for (int j = 0; j < ns; ++j) {
+    const int b = j % NB, bn = (j + 1) % NB;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int c0 = 64 * j + 32 * h;
+      // matrix phase (chunks above every row of this wave are left out); the
+      // next chunk's K as soon as the scores have taken this one's
+      if (c0 <= pos_hi) scores();
+      if (h == 0) read_k(b, 1);
+      else if (j + 1 < ns) read_k(bn, 0);
+      if (c0 >= 32 && c0 - 32 <= pos_hi) output(c0 - 32);
+      // stage j + 1 has landed before any wave reads it, a phase on
+      if (h == 0) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+      phase_end();
+      // vector phase.  Every wave is past its reads of stage j - 1 (the last
+      // were waited for before the barrier just passed), so its buffer takes
+      // stage j + 2
+      if (h == 0 && j + 2 < ns) issue(page_next, (j + 2) % NB);
+      if (h == 1) page_next = page_of(j + 3);
+      __builtin_amdgcn_s_setprio(1);  // (head dim 64: 2% faster)
+      if (c0 <= pos_hi) softmax(c0, b, h);
+      __builtin_amdgcn_s_setprio(0);
+      SPEC_WAIT_VM_LDS(63);  // (LDS reads only)
+      phase_end();
+    }
+  }
+  if (64 * ns - 32 <= pos_hi) output(64 * ns - 32);
+  if (wave < 4) phase_end();
 
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    float lt = lrun[nt];
+    float lt = lrun[nt][0] + lrun[nt][1];
     lt += __shfl_xor(lt, 16, kWave);
     lt += __shfl_xor(lt, 32, kWave);
     const int m = 32 * wave + 16 * nt + l16;
