@@ -62,6 +62,16 @@ AttnPlan plan_attention(const std::vector<AttnSegment>& segs, int G, int Hkv, in
   // head) pairs, at least one 32-key chunk per wave
   long long split = (total_keys * Hkv + target_wgs - 1) / std::max(1, target_wgs);
   split = std::max<long long>(32 * p.w, (split + 31) / 32 * 32);
+  // Short contexts whole: a combine is a launch of 3.5 us or more, and one
+  // workgroup walks 512 keys in less.  Measured on verify forwards of 6 rows a
+  // sequence (12 layers 16q / 16kv head dim 64, 16 layers 32 / 8 / 64, 4 layers
+  // 32 / 8 / 128; 1, 3, 8 and 24 sequences): at up to 512 keys whole is faster
+  // or equal everywhere (8 sequences of up to 500 tokens 557 -> 528 us; 24: 824 ->
+  // 780, 1632 -> 1542, 1021 -> 981 us).  At 1000 it is from 64 workgroups on (8
+  // sequences 1268 -> 1239 and 779 -> 763 us, 24: 1679 -> 1596 and 1043 -> 1001
+  // us), but not at 8 and 24 (390 -> 406 and 1126 -> 1132 us).
+  const long long whole = static_cast<long long>(tiles.size()) * Hkv >= 64 ? 1024 : 512;
+  if (max_keys <= whole) split = std::max<long long>(split, max_keys);
   auto parts_for = [&](long long sp) {
     long long n = 0;
     for (const auto& t : tiles) {
