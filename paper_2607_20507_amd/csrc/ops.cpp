@@ -138,6 +138,7 @@ spec_status spec_sample_draft(int32_t n, const float* logits, int32_t V, const f
   }
   char* ws = static_cast<char*>(workspace);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (n <= kDraftInline) return hip_status(launch_draft_sample_inline(p, rows.data(), seed, tokens, ws + ows, st));
   std::lock_guard<std::mutex> lk(g_mu);
   hipError_t e = stager().upload(ws + odr, rows.data(), sizeof(DRow) * n, st);
   if (e != hipSuccess) return SPEC_E_HIP;

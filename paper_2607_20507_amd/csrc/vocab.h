@@ -132,6 +132,12 @@ hipError_t launch_draft_sample(const DraftPlan& p, const DRow* d_rows, uint64_t 
                                int32_t* d_tokens, void* d_ws, hipStream_t st,
                                const uint64_t* d_seed = nullptr);
 
+// The same with up to kDraftInline rows (host) in the kernel's arguments; row
+// r's token goes to d_tokens[r].
+constexpr int kDraftInline = 64;
+hipError_t launch_draft_sample_inline(const DraftPlan& p, const DRow* rows, uint64_t seed, int32_t* d_tokens,
+                                      void* d_ws, hipStream_t st);
+
 hipError_t launch_philox_uniform(uint64_t seed, uint64_t seq_id, int32_t pos, int32_t purpose,
                                  int32_t n, float* out, hipStream_t st);
 

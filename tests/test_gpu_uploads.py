@@ -1,6 +1,6 @@
 """Call tables on their way to the device: kernel arguments up to 3072 bytes, a
-pinned buffer above.  Draws of n rows (32 bytes of table each) around that
-limit, issued back to back so that the pinned slots are reused, against the
+pinned buffer above.  Draws of n rows (32 bytes of table each; up to 64 rows
+in the arguments of the draw itself) around these limits, issued back to back so that the pinned slots are reused, against the
 same rows drawn one by one."""
 
 import numpy as np
@@ -11,7 +11,7 @@ from tests.gpu_util import device, torch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [1, 2, 95, 96, 97, 700])
+@pytest.mark.parametrize("n", [1, 2, 64, 65, 95, 96, 97, 700])
 def test_draws_of_n_rows(n):
     from paper_2607_20507_amd import binding as B
     dev, V, reps = device(), 512, 12
