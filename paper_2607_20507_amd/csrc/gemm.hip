@@ -267,7 +267,7 @@ __global__ __launch_bounds__(kSkinnyMaxWaves * kWave) void gemm_skinny_bf16(
   const int nrb = FUSE ? (R + 15) / 16 : 1, tiles = (N + 15) / 16;
   const int tile = nrb == 1 ? blockIdx.x : blockIdx.x / (8 * nrb) * 8 + blockIdx.x % 8;
   const int m0 = nrb == 1 ? 0 : blockIdx.x / 8 % nrb * 16;
-  if (tile >= tiles) return;
+  if (FUSE && tile >= tiles) return;
   const int qk_tiles = QKV ? (fu.Hq + fu.Hkv) * fu.hd / 16 : 0;
   // Step s of lane group g reads row 4 s + g of the tile at chunk position
   // `row` (tiled layout): 16 bytes of W[tile * 16 + row][32 s + 8 g ..].  A
