@@ -21,16 +21,16 @@
 //    the gate tile and its up tile); its waves split K and reduce through LDS
 //    in a fixed order (deterministic, no atomics).  M is padded to 16 per
 //    tile; MFMA throughput is ~10x what the weight stream needs.
-//  * mfma4 (R > 128, whole W tiles, K % 256 == 0): resident workgroups that
-//    walk tiles of 64 x 128 to 256 x 256, W straight into registers, X through
-//    LDS, the next tile's operands fetched during the last k-steps of a tile;
-//    split-K with a fixed-order reduction when the grid is small.
-//  * mfma3 (up to 128 rows, and the 4096-wide residual adds of the serving
-//    verify): the same operand paths, one tile per workgroup.
-//  * mfma2 (other shapes above 40 rows, the LM heads above 12): both operands
-//    through LDS by direct-to-LDS loads four k-steps ahead.
-//  * fp32 (the fp32 configuration): a plain LDS-tiled FMA kernel on row-major
-//    weights; no reduced-precision arithmetic.
+//  * mfma2, mfma3, mfma4 (above 40 rows, the LM heads above 12), chosen by
+//    plan_mfma.  mfma2: both operands through LDS by direct-to-LDS loads four
+//    k-steps ahead.  mfma3: W straight into registers, X through LDS, one tile
+//    per workgroup.  mfma4 (R > 128, whole W tiles, K % 256 == 0): the same
+//    operand paths, resident workgroups that walk tiles of 64 x 128 to
+//    256 x 256, the next tile's operands fetched during the last k-steps of a
+//    tile.  All split K with a fixed-order reduction.
+//  * fp32 (the fp32 configuration): row-major weights, no reduced-precision
+//    arithmetic; fp32 MFMAs for K % 4 == 0, a plain LDS-tiled FMA kernel
+//    otherwise.
 
 #include <algorithm>
 #include <cstdio>
@@ -38,6 +38,7 @@
 
 #include "common.h"
 #include "gemm.h"
+#include "gemm_plan.h"
 #include "kv_layout.h"
 
 namespace spec {
@@ -1025,11 +1026,6 @@ __global__ __launch_bounds__(256, 1) void gemm_mfma3_bf16(const bf16_t* __restri
 // QKV 242 -> 176, O 172 -> 117, down 455 -> 360 us.  32 x 32 MFMAs had 5% fewer
 // stall cycles and were 6% slower (more power per flop, lower clock); k-steps
 // started at different places per W tile were 3% slower.
-constexpr int kM4DW = 4, kM4DX = 8, kM4Group = 4;
-
-struct M4Tiles {
-  int MT, NT, S, k_len;  // row tiles, W tiles, K splits and their length
-};
 
 // The compiler does not know that this is an MFMA: nothing may write an
 // operand in the two wait states before it, nor read the accumulator until 18
@@ -1672,59 +1668,6 @@ hipError_t skinny(int R, int N, int K, const void* X, const void* W, void* Y, hi
   return hipGetLastError();
 }
 
-// Split-K of gemm_mfma2_bf16: grids under 192 tiles are split so that
-// tiles x splits fills the 256 CUs about once (k-splits multiples of 128,
-// partials within the workspace).  Returns S and the k-split length.
-int mfma2_splits(int MT, int NT, int R, int Nw, int K, size_t ws_bytes, int* k_len) {
-  int S = 1;
-  if (ws_bytes && MT * NT < 192) {
-    S = std::max(1, std::min(8, 256 / (MT * NT)));
-    while (S > 1 && static_cast<size_t>(S) * R * Nw * sizeof(float) > ws_bytes) --S;
-  }
-  *k_len = ((K + S - 1) / S + 127) / 128 * 128;
-  return (K + *k_len - 1) / *k_len;
-}
-
-// Tile shape of gemm_mfma2_bf16: rows per workgroup 32 MTW (64 .. 256) and W
-// rows per workgroup 32 NTW (64 .. 256), the pair with the least estimated
-// time in a cost model fitted (least squares, median error 10%) to measured
-// launches of every shape at 64, 128 and 364 rows of the 8B/1B-shaped
-// projections: per-step terms for the MFMAs and the LDS loads of a
-// workgroup, times the k-steps and the rounds of workgroups over the 256
-// CUs, plus the split-K partial traffic.  Wide tiles waste rows or feed too
-// few CUs on small problems; narrow ones reload X and W more often.  A split
-// SwiGLU pays its second pass as a launch of its own (≈ 6 us; the residual-add
-// and QKV reductions ride on launches that follow anyway: the RMSNorm and the
-// rotary embedding): with it the 41-128-row gate/up projections take narrow
-// unsplit tiles (41-row 1B-shaped gate/up 19.6 -> 16.9 us, 8B-shaped
-// 40.8 -> 36.2 us).
-struct Mfma2Shape {
-  int mtw, ntw;
-};
-
-Mfma2Shape mfma2_shape(int R, int N, int Nw, int K, size_t ws_bytes, bool swiglu) {
-  Mfma2Shape best{2, 2};
-  double best_t = 1e300;
-  for (int mtw : {2, 4, 6, 8}) {
-    if (32 * mtw > 2 * R + 64) continue;  // tiles far taller than R
-    for (int ntw : {2, 4, 8}) {
-      const int MT = (R + 32 * mtw - 1) / (32 * mtw), NT = (Nw + 32 * ntw - 1) / (32 * ntw);
-      int k_len = K;
-      const int S = mfma2_splits(MT, NT, R, Nw, K, ws_bytes, &k_len);
-      const double rounds = (MT * NT * S + 255) / 256;  // whole rounds of workgroups over the CUs
-      const double steps = rounds * (k_len / 32);
-      const double red_mb = S > 1 ? (S + 1.0) * R * N * 4.0 / 1e6 : 0.0;
-      const double t = 0.0119 * steps * mtw * ntw + 0.0056 * steps * (32.0 * (mtw + ntw)) * 64.0 / 1024.0 +
-                       0.0574 * steps + 0.3048 * red_mb + (S > 1 ? (swiglu ? 6.0 : -6.41) : 0.0);
-      if (t < best_t) {
-        best_t = t;
-        best = {mtw, ntw};
-      }
-    }
-  }
-  return best;
-}
-
 template <int EPI>
 hipError_t splitk_finish(const float* ws, int S, int R, int N, void* Y, hipStream_t st, const int32_t* rm,
                          GemmNorm* norm);
@@ -1793,81 +1736,6 @@ hipError_t mfma2_m(int ntw, int R, int N, int K, const bf16_t* x, const bf16_t* 
   }
 }
 
-// gemm_mfma3_bf16 (weights straight to registers), 192 x 256 tiles for the
-// shapes where it beats gemm_mfma2_bf16, of those that gemm_mfma4_bf16 leaves
-// (residual adds of 4096+ outputs up to 384 rows; K % 256 != 0, a partial W
-// tile or an unaligned output): residual-add projections with K >= 8192 whose
-// grid splits K (the 364-row down projection: 76 -> 64 us), and SwiGLU from
-// 160 rows and store-only projections of 65536+ rows in one pass when the
-// tiles fill the 256 CUs at least 3 / 4 of the way (364-row gate/up 114 -> 97
-// us).
-constexpr int kM3MB = 12, kM3NB = 4, kM3D = 4;
-// Small form: 64-row tiles (MB 4) of 64 NB W rows, K split to fill the CUs,
-// for the drafter's and the target's 41-128-row projections, where every
-// workgroup streams all of X: a 64-row tile streams 4 KB of X per k-step
-// through LDS against the 16 KB of the 192-row form.
-constexpr int kM3sMB = 4;
-
-struct Mfma3Plan {
-  int MT, NT, S, k_len;
-  int nb;  // 0: the 192 x 256 form; else the small form with NB = nb
-};
-
-// NB of the small form for a projection of R rows, or 0 where
-// gemm_mfma2_bf16 is used (more than 128 rows; the 65536+-row LM heads).  From
-// a sweep of NB in {1, 2, 4} against gemm_mfma2_bf16 over 13-150 rows of the
-// 8B- and 1B-shaped projections: a residual add or plain store wants about 64
-// tiles (K split 4 ways), so the narrowest W tile with at most 64 tiles; a
-// SwiGLU, whose split costs a launch of its own, the widest tile that still
-// fills 192 CUs unsplit, else NB = 2.  Measured against gemm_mfma2_bf16:
-// 8B-shaped O projection at 41 rows 13.6 -> 11.3 us, gate/up at 96 rows 47.0 ->
-// 37.9 us, down at 96 rows 31.4 -> 27.6 us; 1B-shaped down at 41 rows 13.5 ->
-// 12.3 us, gate/up at 78 rows 20.1 -> 17.6 us; elsewhere within a few percent.
-int mfma3_small_nb(int R, int Nw, int K, int epi) {
-  (void)K;
-  if (R > 128 || Nw >= 65536) return 0;
-  const int MT = (R + 16 * kM3sMB - 1) / (16 * kM3sMB);
-  auto tiles = [&](int nb) { return MT * ((Nw + 64 * nb - 1) / (64 * nb)); };
-  if (epi == kEpiSwiGLU) return tiles(4) >= 192 ? 4 : 2;
-  for (int nb : {1, 2}) if (tiles(nb) <= 64) return nb;
-  return 4;
-}
-
-bool use_mfma3(int R, int Nw, int K, int epi, size_t ws_bytes, Mfma3Plan* plan = nullptr) {
-  if (K % (32 * kM3D)) return false;
-  if (static_cast<double>(Nw) * K >= 2147483648.0 || static_cast<double>(R) * K >= 2147483648.0) return false;
-  if (R < 160) {
-    const int nb = ws_bytes ? mfma3_small_nb(R, Nw, K, epi) : 0;
-    if (nb == 0 || (epi == kEpiSwiGLU && nb % 2)) return false;
-    const int MT = (R + 16 * kM3sMB - 1) / (16 * kM3sMB), NT = (Nw + 64 * nb - 1) / (64 * nb);
-    int k_len = K;
-    const int S = mfma2_splits(MT, NT, R, Nw, K, ws_bytes, &k_len);  // k_len: a multiple of 128 = 32 D
-    if (plan) *plan = {MT, NT, S, k_len, nb};
-    return true;
-  }
-  const int MT = (R + 16 * kM3MB - 1) / (16 * kM3MB), NT = (Nw + 64 * kM3NB - 1) / (64 * kM3NB);
-  int k_len = K, S = 1;
-  bool ok;
-  if (epi == kEpiAddF32) {
-    S = mfma2_splits(MT, NT, R, Nw, K, ws_bytes, &k_len);  // k_len: a multiple of 128 = 32 D
-    ok = K >= 8192 && S >= 2;
-  } else {
-    ok = (epi == kEpiSwiGLU || (epi == kEpiStoreF32 && Nw >= 65536)) && MT * NT >= 192;
-  }
-  if (!ok && epi == kEpiAddF32 && K < 8192 && Nw >= 4096 && Nw < 65536 && R <= 384) {
-    // the residual-add projections of the 8B-shaped target at 160-384 rows
-    // (the serving verify's O projection): the 64-row form with 256-row W
-    // tiles, K split (364 rows 29.2 -> 25.4 us against gemm_mfma2_bf16)
-    const int MTs = (R + 16 * kM3sMB - 1) / (16 * kM3sMB), NTs = (Nw + 255) / 256;
-    int kl = K;
-    const int Ss = mfma2_splits(MTs, NTs, R, Nw, K, ws_bytes, &kl);
-    if (ws_bytes && plan) *plan = {MTs, NTs, Ss, kl, 4};
-    return ws_bytes != 0;
-  }
-  if (ok && plan) *plan = {MT, NT, S, k_len, 0};
-  return ok;
-}
-
 template <int EPI>
 auto mfma3_kernel(int nb) {
   if constexpr (EPI == kEpiSwiGLU) {
@@ -1895,82 +1763,9 @@ hipError_t mfma3(int R, int N, int K, const bf16_t* x, const bf16_t* w, void* Y,
 }
 
 // ---------------------------------------------------------------------------
-// gemm_mfma4_bf16's tile shape and K split.
-
-struct M4Shape {
-  int mb, nb, occ;      // tile 16 mb rows x 64 nb W rows, workgroups per CU
-  double step, rounds;  // us per 1000 MFMA cycles of a k-step; factor where a launch has several rounds
-};
-// 256 x 256 down to 64 x 128: fewer bytes per flop against more workgroups.
-constexpr M4Shape kM4Shapes[] = {{16, 4, 1, 0.64, 1.0},  {16, 3, 1, 0.62, 1.0},  {12, 4, 1, 0.65, 1.06},
-                                 {8, 4, 1, 0.68, 1.16}, {8, 2, 2, 0.76, 1.16}, {4, 2, 2, 0.90, 1.16}};
-constexpr int kM4Shapes_n = sizeof(kM4Shapes) / sizeof(kM4Shapes[0]);
-
-struct M4Plan {
-  int shape = -1;
-  M4Tiles tl{};
-};
-
-// Estimated time in us, a fit (median error 8%) to 3000 launches of every
-// shape and split on 15 projections at 100 to 8192 rows: a k-step takes the
-// longer (4-norm) of its MFMAs and of its X and W bytes at 80 GB/s per CU
-// (the most a CU takes in), over whole rounds of workgroups; then the output
-// at 4.3 TB/s, and for a split the second pass.  The shape it picks is within
-// 1.1% of the best one on average, 3.6% at the ninetieth percentile.
-double m4_time(const M4Shape& s, int R, int N, int Nw, int K, int epi, int S, bool normed, bool deferred) {
-  const int MT = (R + 16 * s.mb - 1) / (16 * s.mb), NT = (Nw + 64 * s.nb - 1) / (64 * s.nb);
-  const int k_len = ((K + S - 1) / S + 255) / 256 * 256;
-  const int T = MT * NT * S, cap = 256 * s.occ;
-  const double steps = k_len / 32;
-  const double mfma = s.mb * s.nb * 0.016 * s.step;
-  const double in = (std::min(16 * s.mb, R) + 64 * s.nb) * 0.064 * 0.0125;
-  const double tile_mb = 16.0 * s.mb * 64.0 * s.nb * 4e-6 *
-                         (S > 1 ? 1.0 : epi == kEpiAddF32 ? 2.0 : epi == kEpiSwiGLU ? 0.25 : 1.0);
-  auto round = [&](int n) {  // n workgroups at once
-    const double a = n > 256 ? 2.0 * 1.15 * mfma : mfma, b = n > 256 ? 2.0 * in : in;
-    return steps * std::sqrt(std::sqrt(a * a * a * a + b * b * b * b)) + 0.23 * tile_mb * n;
-  };
-  double t = (T / cap) * round(cap) + (T % cap ? round(T % cap) : 0.0);
-  if (T > cap) t *= s.rounds;
-  const double out = R * static_cast<double>(N) / 1e6, part = R * static_cast<double>(Nw) * S / 1e6;
-  if (S > 1) t += deferred ? 0.3 * part : 4.5 + 0.375 * (part + 2.0 * out);
-  else if (normed) t += 3.0 + 1.5 * out;  // the RMSNorm that a split's second pass applies
-  return t;
-}
-
-// Rows above 128 (below, gemm_mfma3_bf16's 64-row form is as fast) of
-// projections of whole W tiles and whole unrolled k-loops.  Residual adds of
-// 4096+ outputs stay with gemm_mfma3_bf16 up to 384 rows: both are bound by
-// what a CU takes in there (382-row down projection 63.7 against 64.1 us, O
-// 26.9 against 25.6-26.0).
-bool plan_mfma4(int R, int N, int K, int epi, size_t ws_bytes, bool normed, bool deferred, M4Plan* plan = nullptr) {
-  const int Nw = epi == kEpiSwiGLU ? 2 * N : N;
-  if (R <= 128 || N % 16 || K % (32 * kM4DX)) return false;
-  if (static_cast<double>(Nw) * K >= 2147483648.0 || static_cast<double>(R) * K >= 2147483648.0) return false;
-  if (epi == kEpiAddF32 && N >= 4096 && R <= 384 && ws_bytes) return false;
-  double best = 1e300;
-  for (int i = 0; i < kM4Shapes_n; ++i) {
-    const M4Shape& s = kM4Shapes[i];
-    if (epi == kEpiSwiGLU && s.nb % 2) continue;
-    const int MT = (R + 16 * s.mb - 1) / (16 * s.mb), NT = (Nw + 64 * s.nb - 1) / (64 * s.nb);
-    for (int S = 1; S <= 8; S *= 2) {
-      const int k_len = ((K + S - 1) / S + 255) / 256 * 256;
-      if (S > 1 && ((K + k_len - 1) / k_len != S || MT * NT * S > 512 * s.occ ||
-                    static_cast<size_t>(S) * R * Nw * sizeof(float) > ws_bytes))
-        continue;
-      const double t = m4_time(s, R, N, Nw, K, epi, S, normed, deferred);
-      if (t < best) {
-        best = t;
-        if (plan) *plan = {i, {MT, NT, S, k_len}};
-      }
-    }
-  }
-  return true;
-}
-
 template <int EPI>
 hipError_t mfma4(int R, int N, int K, const bf16_t* x, const bf16_t* w, void* Y, hipStream_t st, const int32_t* rm,
-                 float* ws, const M4Plan& p, GemmNorm* norm) {
+                 float* ws, const MfmaPlan& p, GemmNorm* norm) {
   using Kern = void (*)(const bf16_t*, const bf16_t*, void*, float*, int, int, int, M4Tiles, const int32_t*);
   Kern k = nullptr;
   switch (p.shape) {
@@ -1994,39 +1789,32 @@ hipError_t mfma4(int R, int N, int K, const bf16_t* x, const bf16_t* w, void* Y,
   return splitk_finish<EPI>(ws, p.tl.S, R, N, Y, st, rm, norm);
 }
 
+// gemm_mfma4_bf16 moves 4 outputs (and partials) at a time.
+bool m4_aligned(int epi, const void* Y, const void* ws) {
+  return reinterpret_cast<uintptr_t>(Y) % (epi == kEpiSwiGLU ? 8 : 16) == 0 &&
+         reinterpret_cast<uintptr_t>(ws) % 16 == 0;
+}
+
+Tail tail_of(int epi, const GemmNorm* norm, const int32_t* rm) {
+  if (!norm || rm) return Tail::kNone;
+  return epi == kEpiAddF32 ? Tail::kNorm : epi == kEpiStoreF32 && norm->defer ? Tail::kRope : Tail::kNone;
+}
+
 template <int EPI>
 hipError_t mfma2(int R, int N, int K, const void* X, const void* W, void* Y, hipStream_t st,
                  const int32_t* rm, float* ws, size_t ws_bytes, GemmNorm* norm = nullptr) {
   const bf16_t* x = static_cast<const bf16_t*>(X);
   const bf16_t* w = static_cast<const bf16_t*>(W);
-  // gemm_mfma4_bf16 moves 4 outputs (and partials) at a time
-  const auto aligned = [](const void* p, unsigned a) { return reinterpret_cast<uintptr_t>(p) % a == 0; };
-  M4Plan p4;
-  if (aligned(Y, EPI == kEpiSwiGLU ? 8 : 16) &&
-      plan_mfma4(R, N, K, EPI, ws && aligned(ws, 16) ? ws_bytes : 0, EPI == kEpiAddF32 && norm && !rm,
-                 EPI == kEpiStoreF32 && norm && norm->defer && !rm, &p4))
-    return mfma4<EPI>(R, N, K, x, w, Y, st, rm, ws, p4, norm);
-  Mfma3Plan p3;
-  if (use_mfma3(R, EPI == kEpiSwiGLU ? 2 * N : N, K, EPI, ws ? ws_bytes : 0, &p3))
-    return mfma3<EPI>(R, N, K, x, w, Y, st, rm, ws, p3, norm);
-  const Mfma2Shape sh = mfma2_shape(R, N, EPI == kEpiSwiGLU ? 2 * N : N, K, ws ? ws_bytes : 0, EPI == kEpiSwiGLU);
+  const MfmaPlan p = plan_mfma(R, N, K, EPI, ws ? ws_bytes : 0, m4_aligned(EPI, Y, ws), tail_of(EPI, norm, rm));
+  if (p.kernel == MfmaPlan::kM4) return mfma4<EPI>(R, N, K, x, w, Y, st, rm, ws, p, norm);
+  if (p.kernel == MfmaPlan::kM3) return mfma3<EPI>(R, N, K, x, w, Y, st, rm, ws, p.m3, norm);
+  const Mfma2Shape sh = p.m2;
   switch (sh.mtw) {
     case 2: return mfma2_m<EPI, 2>(sh.ntw, R, N, K, x, w, Y, st, rm, ws, ws_bytes, norm);
     case 4: return mfma2_m<EPI, 4>(sh.ntw, R, N, K, x, w, Y, st, rm, ws, ws_bytes, norm);
     case 6: return mfma2_m<EPI, 6>(sh.ntw, R, N, K, x, w, Y, st, rm, ws, ws_bytes, norm);
     default: return mfma2_m<EPI, 8>(sh.ntw, R, N, K, x, w, Y, st, rm, ws, ws_bytes, norm);
   }
-}
-
-// Skinny (weight streaming, X re-read per 16-feature tile) or MFMA tiles (X
-// staged once per workgroup tile): measured at 9..64 rows on the 8B- and
-// 1B-shaped projections, the MFMA kernel wins above 40 rows, above 12 rows
-// for long reductions (K >= 8192) and the 128256-row LM heads, and above 24
-// rows for projections of >= 16M weights.
-bool use_mfma(int R, int Nw, int K) {
-  if (R > 40) return true;
-  if (R > 12 && (K >= 8192 || Nw >= 65536)) return true;
-  return R > 24 && static_cast<double>(Nw) * K >= 16.0 * (1 << 20);
 }
 
 template <int EPI>
@@ -2056,14 +1844,6 @@ hipError_t launch_pack_weight(void* W, int rows, int K, int rot_rows, int hd, hi
   const size_t lds = static_cast<size_t>(G) * 16 * sizeof(u32x4);
   pack_weight_kernel<<<groups * (K / 128), 256, lds, st>>>(static_cast<bf16_t*>(W), rows, K, rot_rows, hd);
   return hipGetLastError();
-}
-
-size_t gemm_splitk_bytes(int R_max, int Nw_max) {
-  // only grids of fewer than 192 tiles split, into S <= min(8, 256 / tiles)
-  // parts; tiles >= R Nw / (256 * 256), so the partials S R Nw stay below
-  // 256 * 256 * 256 floats (and below 8 R Nw)
-  const double cap = std::min(8.0 * R_max * Nw_max, 256.0 * 256.0 * 256.0);
-  return static_cast<size_t>(cap) * sizeof(float);
 }
 
 hipError_t launch_gemm_fused(int R, int N, int K, const void* X, const void* W, void* Y, int epi,
@@ -2140,11 +1920,11 @@ const char* gemm_kernel_name(int dtype, int R, int N, int K, int epi, bool fused
           snprintf(m4[e][i], sizeof(m4[e][i]), "gemm_mfma4_bf16<%d, %d, %d, %d>", e, kM4Shapes[i].mb, kM4Shapes[i].nb,
                    kM4Shapes[i].occ);
     });
-    M4Plan p4;
-    if (plan_mfma4(R, N, K, epi, splitk_bytes, normed, deferred, &p4)) return m4[epi][p4.shape];
-    Mfma3Plan p3;
-    if (use_mfma3(R, Nw, K, epi, splitk_bytes, &p3)) return m3[epi][p3.nb];
-    const Mfma2Shape sh = mfma2_shape(R, N, Nw, K, splitk_bytes, epi == kEpiSwiGLU);
+    const MfmaPlan p = plan_mfma(R, N, K, epi, splitk_bytes, true,
+                                 normed ? Tail::kNorm : deferred ? Tail::kRope : Tail::kNone);
+    if (p.kernel == MfmaPlan::kM4) return m4[epi][p.shape];
+    if (p.kernel == MfmaPlan::kM3) return m3[epi][p.m3.nb];
+    const Mfma2Shape sh = p.m2;
     return tiled[epi][sh.mtw / 2 - 1][sh.ntw == 2 ? 0 : (sh.ntw == 4 ? 1 : 2)];
   }
   return names[(std::max(R, 1) - 1) / 16][epi][0];

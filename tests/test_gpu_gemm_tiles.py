@@ -1,7 +1,9 @@
-"""The projections of more than 128 rows: every tile shape and K split of the
-resident-workgroup MFMA GEMM at the sizes where tiles, splits and loops end
-(one row past a tile, one 16-feature W tile, the shortest k-loop), against
-float64, with and without the split-K workspace.
+"""The projections of more than 128 rows against float64, with and without the
+split-K workspace: sizes where tiles, splits and loops end (one row past a
+tile, one 16-feature W tile, the shortest k-loop) whatever kernel takes them,
+and one for every form of the resident-workgroup MFMA GEMM (epilogue, tile, K
+split, one or several tiles per workgroup) that the planner returns for the
+configured models (a CPU test holds the list to that).
 
 Tolerance: a sum of K bf16 products in fp32, in any order, is within K 2^-24
 sum |x w| of the exact one; for normal inputs that is sqrt(K) 2^-24 of the
@@ -25,6 +27,23 @@ CASES = [
     (129, 16, 256), (129, 1040, 512), (192, 2048, 2048), (193, 272, 1024), (256, 4096, 4096), (257, 1024, 2816),
     (385, 4112, 768), (500, 6144, 1024), (640, 2816, 1024), (1000, 3072, 2048), (1025, 2048, 8192), (2049, 6160, 512),
     (4111, 1024, 1024), (5000, 4096, 256),
+]
+
+
+# epilogue, rows, outputs, K: partial tiles on both sides, several tiles of three unrolled k-loops
+FORMS = [
+    (STORE, 129, 272, 256), (STORE, 193, 16448, 256), (STORE, 1706, 272, 1536), (STORE, 259, 6640, 256),
+    (STORE, 271, 4160, 2816), (STORE, 259, 13072, 512), (STORE, 774, 17360, 768), (STORE, 262, 8272, 8192),
+    (STORE, 526, 14528, 256), (STORE, 906, 16464, 768), (STORE, 649, 14896, 256), (STORE, 990, 16784, 768),
+    (STORE, 196, 16848, 4096), (STORE, 644, 16736, 512), (STORE, 1420, 16784, 768), (STORE, 580, 8256, 6144),
+    (ADD, 130, 272, 256), (ADD, 1684, 272, 1536), (ADD, 197, 464, 1024), (ADD, 323, 6096, 256),
+    (ADD, 259, 3472, 2048), (ADD, 200, 2064, 2048), (ADD, 257, 912, 4096), (ADD, 257, 13120, 512),
+    (ADD, 196, 5408, 6144), (ADD, 260, 1568, 10240), (ADD, 516, 14624, 256), (ADD, 907, 16448, 768),
+    (ADD, 258, 12368, 4096), (ADD, 258, 6432, 4096), (ADD, 584, 1952, 8192), (ADD, 6360, 1328, 256),
+    (ADD, 1924, 8208, 768), (ADD, 6646, 528, 2816), (ADD, 641, 16672, 512), (ADD, 1423, 16400, 768),
+    (ADD, 596, 8352, 5120), (ADD, 193, 12480, 8192), (SWIGLU, 130, 272, 256), (SWIGLU, 130, 10960, 256),
+    (SWIGLU, 264, 3296, 256), (SWIGLU, 258, 6560, 512), (SWIGLU, 263, 16432, 768), (SWIGLU, 517, 7392, 256),
+    (SWIGLU, 390, 16736, 768), (SWIGLU, 395, 12992, 512), (SWIGLU, 666, 16560, 768),
 ]
 
 
@@ -67,6 +86,11 @@ def test_projection(R, N, K, epi, workspace):
     scale = want.pow(2).mean().sqrt()
     lim = (2 ** -8 * want.abs() if epi == SWIGLU else 0.0) + 64 * K ** 0.5 * 2 ** -24 * scale
     assert torch.all((got - want).abs() <= lim)
+
+
+@pytest.mark.parametrize("epi,R,N,K", FORMS)
+def test_form(epi, R, N, K):
+    test_projection(R, N, K, epi, True)
 
 
 def test_unaligned_output_takes_the_general_path():
