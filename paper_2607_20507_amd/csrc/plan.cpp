@@ -70,7 +70,14 @@ AttnPlan plan_attention(const std::vector<AttnSegment>& segs, int G, int Hkv, in
   // 780, 1632 -> 1542, 1021 -> 981 us).  At 1000 it is from 64 workgroups on (8
   // sequences 1268 -> 1239 and 779 -> 763 us, 24: 1679 -> 1596 and 1043 -> 1001
   // us), but not at 8 and 24 (390 -> 406 and 1126 -> 1132 us).
-  const long long whole = static_cast<long long>(tiles.size()) * Hkv >= 64 ? 1024 : 512;
+  // The widest tiles (64 query vectors, two waves: a wave walks twice the keys
+  // at twice the work each) gain less and lose sooner: 16 rows x 4 query heads
+  // of 8 sequences over 1016 keys, head dim 128 (64 workgroups), 34 us split
+  // and 55 whole, 48 vectors over 506 keys (24 workgroups) 22 and 33.  Whole is
+  // faster there up to 128 keys (9 to 64 workgroups: 10% on average), 192 from
+  // 64 workgroups on (25%) and 512 from 256 (25-30%).
+  const long long wgs = static_cast<long long>(tiles.size()) * Hkv;
+  const long long whole = p.nt < 4 ? (wgs >= 64 ? 1024 : 512) : (wgs >= 256 ? 512 : wgs >= 64 ? 192 : 128);
   if (max_keys <= whole) split = std::max<long long>(split, max_keys);
   auto parts_for = [&](long long sp) {
     long long n = 0;

@@ -153,3 +153,24 @@ def test_plan_batch1_shapes(plan_exe):
     # the single 6-row verify: two 4- and 2-row tiles, 128-key ranges (17 partials each)
     assert sorted({(it[0], it[1]) for it in plans[0]["items"]}) == [(0, 4), (4, 2)]
     assert plans[0]["n_parts"] == 34
+
+
+@pytest.mark.parametrize("G,Hkv,n_seq,rows,pos0,whole", [
+    # (measured us, head dim 128: whole / split)
+    (4, 8, 8, 16, 1000, False),   # 64 query vectors, 64 workgroups: 55 / 34
+    (8, 1, 24, 6, 500, False),    # 48 vectors, 24 workgroups: 33 / 22
+    (8, 8, 3, 6, 500, False),     # 48 vectors, 24 workgroups: 28 / 21
+    (8, 1, 24, 6, 200, False),    # 23.2 / 20
+    (8, 1, 24, 6, 100, True),
+    (8, 8, 24, 6, 180, True),     # 192 workgroups
+    (8, 4, 64, 6, 500, True),     # 256 workgroups: 35.3 / 38.3
+    (8, 4, 64, 6, 700, False),    # 44.0 / 42.8
+    (4, 8, 8, 6, 1000, True),     # 24 vectors: 512 keys whole, 1024 from 64 workgroups on
+    (4, 8, 2, 6, 500, True),
+    (4, 8, 2, 6, 1000, False),
+])
+def test_short_contexts_whole(plan_exe, G, Hkv, n_seq, rows, pos0, whole):
+    segs = [(s, rows * s, rows, pos0) for s in range(n_seq)]
+    plan, = run_plans(plan_exe, [(G, Hkv, 4096, 512, True, segs)])
+    check_plan(plan, G, Hkv, 4096, segs)
+    assert (not plan["groups"]) == whole
