@@ -379,9 +379,10 @@ spec_status launch_forward(spec_ctx* ctx, const Model& M, const FwdOff& o, const
   // outputs (read-modify-write for the residual add), flops = 2 R N_w K.
   auto gemm = [&](int rows, int N, int K, const void* X, const void* W, void* Y, int epi,
                   const int32_t* rm, const GemmFuse* f = nullptr, GemmNorm* nrm = nullptr) -> hipError_t {
-    const bool timed = tm.wants(gemm_kernel_name(dt, rows, N, K, epi, f != nullptr, ctx->ws.splitk_bytes,
-                                                 epi == kEpiAddF32 && nrm && !rm,
-                                                 epi == kEpiStoreF32 && nrm && nrm->defer && !rm));
+    // (the name plans the launch a second time: asked for only while a kernel is timed)
+    const bool timed = tm.on() && tm.wants(gemm_kernel_name(dt, rows, N, K, epi, f != nullptr, ctx->ws.splitk_bytes,
+                                                            epi == kEpiAddF32 && nrm && !rm,
+                                                            epi == kEpiStoreF32 && nrm && nrm->defer && !rm));
     if (timed) tm.begin(st);
     const hipError_t e =
         f ? launch_gemm_fused(rows, N, K, X, W, Y, epi, *f, st, rm)

@@ -38,6 +38,7 @@ class EventTimer : public KernelTimer {
     flush();
     for (hipEvent_t e : free_) (void)hipEventDestroy(e);
   }
+  bool on() const { return !name.empty(); }
   bool wants(const char* k) const override { return !name.empty() && name == k; }
   // begin arms a kernel-level event pair for the next launch_kernel (the
   // timed kernel's own start and end) and also records an event on the
