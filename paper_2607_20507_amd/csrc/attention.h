@@ -8,7 +8,7 @@ namespace spec {
 
 // One unit of work: rows [row0, row0 + nrows) of one sequence (positions
 // pos0.. consecutive) against keys [t0, t1) of that sequence, for all kv heads
-// (grid.y).  part >= 0: write an unnormalised partial for a later combine;
+// (adjacent blocks).  part >= 0: write an unnormalised partial for a later combine;
 // part < 0: write the normalised output.
 struct AttnItem {
   int32_t row0, nrows, pos0, seq, t0, t1, part, pad;
@@ -51,7 +51,7 @@ hipError_t launch_attention_bf16(const AttnArgs& a, const AttnItem* d_items, int
 hipError_t launch_attention_prefill_bf16(const AttnArgs& a, const AttnItem* d_items, int n_items, hipStream_t st);
 const char* attn_prefill_kernel_name(int hd);
 
-// fp32: one wave per (row, head); row r of sequence slot row_seq[r] at
+// fp32: one workgroup of 256 threads per (row, head); row r of sequence slot row_seq[r] at
 // position row_pos[r] attends keys 0..row_pos[r] (or its tree keys).
 hipError_t launch_attention_f32(const AttnArgs& a, int R, const int32_t* d_row_seq,
                                 const int32_t* d_row_pos, hipStream_t st);

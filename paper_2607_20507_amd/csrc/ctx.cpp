@@ -395,8 +395,9 @@ spec_status launch_forward(spec_ctx* ctx, const Model& M, const FwdOff& o, const
     }
     return e;
   };
-  // Above 8 rows each RMSNorm is its own kernel, unless the residual-add GEMM
-  // before it splits K: then the split-K reduction applies it (GemmNorm).
+  // Past the fused path's rows each RMSNorm is its own kernel, unless the
+  // residual-add GEMM before it splits K: then the split-K reduction applies it
+  // (GemmNorm).
   bool normed = false;  // y already holds the next RMSNorm's rows
   for (int l = 0; l < d.n_layers; ++l) {
     const auto& L = M.layers[l];

@@ -54,8 +54,10 @@ __global__ __launch_bounds__(256) void upload_mapped_kernel(const uint32_t* __re
 }
 
 // The rotation angles of one row, by the last threads of the workgroup.  Once
-// per forward: evaluated by every layer's QKV epilogue and rope_kv, the fp64
-// arithmetic was @ROT@
+// per forward: evaluated in every layer's QKV epilogue and rope_kv instead, the
+// fp64 arithmetic made forwards of 6 to 16 rows 1-3% longer (8 rows, 16 layers of
+// 2048 x 16384 828 us against 807; 16 rows, 12 layers of 1024 x 5632 447 against
+// 438), others up to 2%, none shorter.
 __device__ __forceinline__ void row_angles(const RotTable& rot, int r) {
   if (!rot.ang) return;
   const int half = rot.hd / 2;

@@ -69,7 +69,7 @@ struct GemmNorm {
 // row_map (device, optional): output row m goes to Y row row_map[m].
 // splitk_ws (device, optional): fp32 partials for split-K on small grids
 // (R > 64); without it the kernel does not split K.
-// norm (optional, kEpiAddF32 only): see GemmNorm.
+// norm (optional, kEpiAddF32, or kEpiStoreF32 with defer set): see GemmNorm.
 hipError_t launch_gemm(int dtype, int R, int N, int K, const void* X, const void* W, void* Y,
                        int epi, hipStream_t st, const int32_t* row_map = nullptr,
                        float* splitk_ws = nullptr, size_t splitk_bytes = 0, GemmNorm* norm = nullptr);

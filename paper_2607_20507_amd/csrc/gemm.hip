@@ -1207,7 +1207,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma4_bf16(const bf16_t* __rest
 
     // Lane (l16, g) holds rows 4 g + r of column l16 of each 16 x 16 block;
     // after the quad transpose row 4 g + l16 % 4, columns 4 (l16 / 4) .. + 3.
-    // The residual rows are read kM4Pre row blocks ahead (with each block's
+    // The residual rows are read PRE row blocks ahead (with each block's
     // loads behind the last one's stores the 4096-row O projection's add took
     // 45 of 180 thousand cycles).
     const int m0 = cur.mt * TM, f0 = cur.nt * (SW ? 8 * NTG : 16 * NTG);

@@ -151,7 +151,8 @@ hipError_t launch_upload_mapped(void* dst, const void* src, size_t n, hipStream_
 // GPU.  With hipMemcpyAsync, whose copies above a few KB go to a copy engine
 // that the kernel behind them then waits for, the attention call of 64
 // sequences (64 KB of page ids) took 105 us against 91, the decision pass of
-// 256 (130 KB) 377 against 364, a draw for 8 rows 20 against 18.
+// 256 (130 KB) 377 against 364, a draw for 8 rows (whose table the draw's own
+// arguments carry by now) 20 against 18.
 // Destinations that are not 16-byte aligned and blocks above kMappedMax (a
 // copy engine moves those faster than a kernel's reads over PCIe) still copy.
 class Stager {
