@@ -48,8 +48,11 @@ hipError_t launch_attention_bf16(const AttnArgs& a, const AttnItem* d_items, int
 // bf16 causal prefill: items from plan_attention's prefill form (blocks of
 // 256 / G consecutive rows of one sequence against keys 0 .. t1 - 1, t0 = 0,
 // part < 0), heaviest first; grid n_items x Hkv (kv head = block % Hkv).
-hipError_t launch_attention_prefill_bf16(const AttnArgs& a, const AttnItem* d_items, int n_items, hipStream_t st);
-const char* attn_prefill_kernel_name(int hd);
+// few_keys: every item has at most kPrefillShortKeys keys.
+constexpr int kPrefillShortKeys = 384;
+hipError_t launch_attention_prefill_bf16(const AttnArgs& a, const AttnItem* d_items, int n_items, bool few_keys,
+                                         hipStream_t st);
+const char* attn_prefill_kernel_name(int hd, bool few_keys);
 
 // fp32: one workgroup of 256 threads per (row, head); row r of sequence slot row_seq[r] at
 // position row_pos[r] attends keys 0..row_pos[r] (or its tree keys).

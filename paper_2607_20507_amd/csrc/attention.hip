@@ -384,6 +384,11 @@ __global__ __launch_bounds__(64 * W, NT <= 2 ? 2 : 1) void attn_tree_bf16_kernel
 // (512 cycles) and vector instructions (560) add up to, so the softmax is kept
 // short: 8192 rows (32q / 8kv, head dim 128) 559 -> 490 us (970 -> 1120
 // TFLOP/s), 2048 rows 89 -> 69 us, head dim 64 at 4096 rows 127 -> 114 us.
+// That start and the last output update cost about 1 us, so up to
+// kPrefillShortKeys keys a wave takes its chunks one after another with one
+// barrier per stage (SHORT): 64 / 250 / 300 / 380 keys, 8q / 8kv, head dim 128,
+// 6.8 / 14.6 / 15.5 / 16.3 us by phases, 6.1 / 13.0 / 14.1 / 15.2 in turn; from
+// 500 keys on the phases are as fast or faster.
 // The running maximum of a query vector is raised only when a score exceeds
 // it by more than 2^8 (scores are base-2 logits): each lane compares its own
 // 8 scores against it, and only when some lane of the wave finds a larger
@@ -394,8 +399,8 @@ __global__ __launch_bounds__(64 * W, NT <= 2 ? 2 : 1) void attn_tree_bf16_kernel
 constexpr float kPrefillRescaleLog2 = 8.f;
 constexpr int kPrefillStagedPages = 1024;  // page ids kept in LDS (16384 keys)
 
-template <int HD>
-__global__ __launch_bounds__(512, 1) void attn_prefill_bf16_kernel(AttnArgs a, const AttnItem* __restrict__ items) {
+template <int HD, bool SHORT>
+__device__ __forceinline__ void attn_prefill_body(const AttnArgs& a, const AttnItem* __restrict__ items) {
   constexpr int DS = HD / 32;    // MFMA k-steps over the head dim
   constexpr int DT = HD / 16;    // 16-dim output tiles
   constexpr int NT = 2;          // 16-vector query tiles per wave
@@ -588,44 +593,69 @@ __global__ __launch_bounds__(512, 1) void attn_prefill_bf16_kernel(AttnArgs a, c
   };
 
   issue(page_of(0), 0);
-  if (ns > 1) {
-    issue(page_of(1), 1);
-    SPEC_WAIT_VM_LDS(LPW);
-  } else {
-    SPEC_WAIT_VM_LDS(0);
-  }
-  int page_next = page_of(2);
-  phase_end();  // stage 0 has landed
-  read_k(0, 0);
-  if (wave >= 4) phase_end();  // waves 4..7 run one phase behind
-  for (int j = 0; j < ns; ++j) {
-    const int b = j % NB, bn = (j + 1) % NB;
+  if (ns > 1) issue(page_of(1), 1);
+  if constexpr (SHORT) {
+    for (int j = 0; j < ns; ++j) {
+      // stage j has landed (stage j + 1 may be in flight), every wave is done
+      // with stage j - 1, whose buffer takes stage j + 2
+      if (j + 1 < ns) {
+        SPEC_WAIT_VM_LDS(LPW);
+      } else {
+        SPEC_WAIT_VM_LDS(0);
+      }
+      phase_end();
+      if (j + 2 < ns) issue(page_of(j + 2), (j + 2) % NB);
+      const int b = j % NB;
+      read_k(b, 0);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int c0 = 64 * j + 32 * h;
-      // matrix phase (chunks above every row of this wave are left out); the
-      // next chunk's K as soon as the scores have taken this one's
-      if (c0 <= pos_hi) scores();
-      if (h == 0) read_k(b, 1);
-      else if (j + 1 < ns) read_k(bn, 0);
-      if (c0 >= 32 && c0 - 32 <= pos_hi) output(c0 - 32);
-      // stage j + 1 has landed before any wave reads it, a phase on
-      if (h == 0) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-      phase_end();
-      // vector phase.  Every wave is past its reads of stage j - 1 (the last
-      // were waited for before the barrier just passed), so its buffer takes
-      // stage j + 2
-      if (h == 0 && j + 2 < ns) issue(page_next, (j + 2) % NB);
-      if (h == 1) page_next = page_of(j + 3);
-      __builtin_amdgcn_s_setprio(1);  // (head dim 64: 2% faster)
-      if (c0 <= pos_hi) softmax(c0, b, h);
-      __builtin_amdgcn_s_setprio(0);
-      SPEC_WAIT_VM_LDS(63);  // (LDS reads only)
-      phase_end();
+      for (int h = 0; h < 2; ++h) {
+        const int c0 = 64 * j + 32 * h;
+        if (c0 > pos_hi) break;  // above every row of this wave
+        scores();
+        if (h == 0) read_k(b, 1);
+        softmax(c0, b, h);
+        output(c0);
+      }
     }
+  } else {
+    if (ns > 1) {
+      SPEC_WAIT_VM_LDS(LPW);
+    } else {
+      SPEC_WAIT_VM_LDS(0);
+    }
+    int page_next = page_of(2);
+    phase_end();  // stage 0 has landed
+    read_k(0, 0);
+    if (wave >= 4) phase_end();  // waves 4..7 run one phase behind
+    for (int j = 0; j < ns; ++j) {
+      const int b = j % NB, bn = (j + 1) % NB;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int c0 = 64 * j + 32 * h;
+        // matrix phase (chunks above every row of this wave are left out); the
+        // next chunk's K as soon as the scores have taken this one's
+        if (c0 <= pos_hi) scores();
+        if (h == 0) read_k(b, 1);
+        else if (j + 1 < ns) read_k(bn, 0);
+        if (c0 >= 32 && c0 - 32 <= pos_hi) output(c0 - 32);
+        // stage j + 1 has landed before any wave reads it, a phase on
+        if (h == 0) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        phase_end();
+        // vector phase.  Every wave is past its reads of stage j - 1 (the last
+        // were waited for before the barrier just passed), so its buffer takes
+        // stage j + 2
+        if (h == 0 && j + 2 < ns) issue(page_next, (j + 2) % NB);
+        if (h == 1) page_next = page_of(j + 3);
+        __builtin_amdgcn_s_setprio(1);  // (head dim 64: 2% faster)
+        if (c0 <= pos_hi) softmax(c0, b, h);
+        __builtin_amdgcn_s_setprio(0);
+        SPEC_WAIT_VM_LDS(63);  // (LDS reads only)
+        phase_end();
+      }
+    }
+    if (64 * ns - 32 <= pos_hi) output(64 * ns - 32);
+    if (wave < 4) phase_end();
   }
-  if (64 * ns - 32 <= pos_hi) output(64 * ns - 32);
-  if (wave < 4) phase_end();
 
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
@@ -643,6 +673,16 @@ __global__ __launch_bounds__(512, 1) void attn_prefill_bf16_kernel(AttnArgs a, c
           make_uint2(pack_bf16x2(v[0] * inv, v[1] * inv), pack_bf16x2(v[2] * inv, v[3] * inv));
     }
   }
+}
+
+template <int HD>
+__global__ __launch_bounds__(512, 1) void attn_prefill_bf16_kernel(AttnArgs a, const AttnItem* __restrict__ items) {
+  attn_prefill_body<HD, false>(a, items);
+}
+template <int HD>
+__global__ __launch_bounds__(512, 1) void attn_prefill_short_bf16_kernel(AttnArgs a,
+                                                                         const AttnItem* __restrict__ items) {
+  attn_prefill_body<HD, true>(a, items);
 }
 
 template <int HD, int DPT>
@@ -885,17 +925,18 @@ hipError_t launch_attention_bf16(const AttnArgs& a, const AttnItem* d_items, int
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_attention_prefill_bf16(const AttnArgs& a, const AttnItem* d_items, int n_items, hipStream_t st) {
+hipError_t launch_attention_prefill_bf16(const AttnArgs& a, const AttnItem* d_items, int n_items, bool few_keys,
+                                         hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
-  if (256 % (a.Hq / a.Hkv)) return hipErrorInvalidValue;
-  dim3 grid(n_items * a.Hkv);
-  if (a.hd == 128) launch_kernel(attn_prefill_bf16_kernel<128>, grid, dim3(512), 0, st, a, d_items);
-  else if (a.hd == 64) launch_kernel(attn_prefill_bf16_kernel<64>, grid, dim3(512), 0, st, a, d_items);
-  else return hipErrorInvalidValue;
+  if (256 % (a.Hq / a.Hkv) || (a.hd != 64 && a.hd != 128)) return hipErrorInvalidValue;
+  auto* k = a.hd == 128 ? (few_keys ? attn_prefill_short_bf16_kernel<128> : attn_prefill_bf16_kernel<128>)
+                        : (few_keys ? attn_prefill_short_bf16_kernel<64> : attn_prefill_bf16_kernel<64>);
+  launch_kernel(k, dim3(n_items * a.Hkv), dim3(512), 0, st, a, d_items);
   return hipGetLastError();
 }
 
-const char* attn_prefill_kernel_name(int hd) {
+const char* attn_prefill_kernel_name(int hd, bool few_keys) {
+  if (few_keys) return hd == 128 ? "attn_prefill_short_bf16_kernel<128>" : "attn_prefill_short_bf16_kernel<64>";
   return hd == 128 ? "attn_prefill_bf16_kernel<128>" : "attn_prefill_bf16_kernel<64>";
 }
 

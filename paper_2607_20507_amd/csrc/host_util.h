@@ -217,7 +217,8 @@ struct AttnSegment {
 };
 
 struct AttnPlan {
-  bool prefill = false;  // items for attn_prefill_bf16_kernel (nt, w, groups unused)
+  bool prefill = false;   // items for the prefill kernel (nt, w, groups unused) ...
+  bool few_keys = false;  // ... of at most kPrefillShortKeys keys each
   int nt = 1;
   int w = 1;  // waves per workgroup
   std::vector<AttnItem> items;

@@ -303,7 +303,7 @@ spec_status spec_op_attention(int32_t dtype, int32_t n_seqs, const int32_t* rows
                                                        n_kv_heads * 64 * head_dim));
   if (a.dtype == 1 && plan.prefill)
     return hip_status(launch_attention_prefill_bf16(a, reinterpret_cast<const AttnItem*>(ws + oit),
-                                                    static_cast<int>(plan.items.size()), st));
+                                                    static_cast<int>(plan.items.size()), plan.few_keys, st));
   if (a.dtype == 1)
     return hip_status(launch_attention_bf16(a, reinterpret_cast<const AttnItem*>(ws + oit),
                                             static_cast<int>(plan.items.size()),

@@ -19,6 +19,7 @@ AttnPlan plan_attention(const std::vector<AttnSegment>& segs, int G, int Hkv, in
   if (allow_prefill && !segs.empty() && min_rows >= kPrefillMinRows && G >= 1 && 256 % G == 0 &&
       max_keys <= kPrefillMaxKeys) {
     p.prefill = true;
+    p.few_keys = max_keys <= kPrefillShortKeys;
     const int br = 256 / G;
     for (const auto& s : segs)
       for (int r = 0; r < s.nrows; r += br) {

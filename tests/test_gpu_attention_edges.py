@@ -60,3 +60,10 @@ def test_probabilities_below_the_normal_range(pos0, hd):
         want = 16 * e * 2.0 ** 126 / (16 * e + pos0 + r + 1 - 16)
         got = out[r].double().cpu().numpy()
         assert np.all(np.abs(got - want) < 2.0 ** -6 * want), (got[0], want)
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("rows,pos0", [([64, 64], [0, 320]), ([300], [0]), ([384], [0]), ([385], [0]), ([64], [321]),
+                                       ([100, 70, 65], [284, 1, 200])])
+def test_prefill_on_both_sides_of_few_keys(rows, pos0, hd):
+    assert _attn_case(1, rows, pos0, 8, 2, hd, seed=sum(rows) + hd + 1) < 1.5e-2
