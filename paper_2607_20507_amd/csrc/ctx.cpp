@@ -314,20 +314,27 @@ FwdOff add_forward(spec_ctx* ctx, const Model& M, const Fwd& f, MetaBlock& mb) {
   return o;
 }
 
-// Rows of the fused path: one 16-row MFMA block of any model; up to
-// kFusedMaxRows, a workgroup per 16 rows, where the layer's projections are at
-// most 16M weights, which the 8 L2s (32 MB) hold while the row blocks read
-// them.  Measured forward against five more launches a layer (RMSNorms in the
-// split-K reductions, rope_kv, the SwiGLU's second pass), contexts 400: 12
-// layers of 1024 x 5632 at 10 / 32 / 64 rows 459 / 594 / 680 -> 414 / 500 /
-// 551 us; 16 layers of 2048 x 16384 at 10 / 16 rows 981 / 1083 -> 852 / 1000,
-// but at 18 and 48 rows 1124 -> 1204 and 1232 -> 1541 us; 4 layers of 4096 x
-// 28672 at 10 / 16 rows 608 / 696 -> 581 / 638, at 18 rows 726 -> 920 us.  (Whole
-// rows per workgroup, W read once: 1232 -> 1595 us at 48 rows, since every
-// 16-feature tile takes in all of X.)  The LM head stays with the tiled GEMM
-// from 9 rows on (16 layers of 2048 x 16384 at 10 rows: 852 us, fused 882).
-constexpr int kFusedRows = 16, kFusedLmRows = 8;
-constexpr long long kFusedSmallWeights = 16LL << 20;
+// Rows of the fused path: one 16-row MFMA block, 12 rows for models wider than
+// 4096; up to kFusedMaxRows, a workgroup per 16 rows, where the layer's largest
+// projection is at most 16M weights, which the 8 L2s (32 MB) hold while the row
+// blocks read them, and rows x weights stay below 512M.  Measured forward
+// against five more launches a layer (RMSNorms in the split-K reductions,
+// rope_kv, the SwiGLU's second pass), contexts 300 to 400: 12 layers of 1024 x
+// 5632 at 10 / 32 / 64 rows 459 / 594 / 680 -> 414 / 500 / 551 us; 12 layers of
+// 1536 x 8192 at 32 / 48 / 64 rows 1.00 / 0.98 / 0.97 times as fast; 16 layers of
+// 2048 x 16384 at 10 / 16 rows 981 / 1083 -> 852 / 1000, but at 18 and 48 rows 1124 ->
+// 1204 and 1232 -> 1541 us; 4 layers of 4096 x 28672 at 10 / 16 rows 608 / 696 ->
+// 581 / 638, at 18 rows 726 -> 920 us; 4 layers of 5120 x 27648 at 12 / 16 rows 697 /
+// 717 -> 665 / 749, 3 of 6144 x 32768 657 / 649 -> 640 / 686.  (Whole rows per
+// workgroup, W read once: 1232 -> 1595 us at 48 rows, since every 16-feature tile
+// takes in all of X.)  The LM head stays with the tiled GEMM from 9 rows on (16
+// layers of 2048 x 16384 at 10 rows: 852 us, fused 882).
+constexpr int kFusedLmRows = 8;
+int fused_rows(int d_model, long long weights) {
+  if (weights <= (16LL << 20))
+    return static_cast<int>(std::min<long long>(kFusedMaxRows, std::max(16LL, ((512LL << 20) - 1) / weights)));
+  return d_model <= 4096 ? 16 : 12;
+}
 
 spec_status launch_forward(spec_ctx* ctx, const Model& M, const FwdOff& o, const char* dev,
                            float* logits, hipStream_t st) {
@@ -348,8 +355,7 @@ spec_status launch_forward(spec_ctx* ctx, const Model& M, const FwdOff& o, const
   // applies RoPE and writes q and the KV cache itself.
   const long long most = std::max({static_cast<long long>(M.qkvw()) * d.d_model, 2LL * d.ffn_dim * d.d_model,
                                    static_cast<long long>(M.qdim()) * d.d_model});
-  const int fused_rows = most <= kFusedSmallWeights ? kFusedMaxRows : kFusedRows;
-  const bool fused = dt == 1 && R <= fused_rows && d.head_dim % 16 == 0 && d.d_model % 16 == 0;
+  const bool fused = dt == 1 && R <= fused_rows(d.d_model, most) && d.head_dim % 16 == 0 && d.d_model % 16 == 0;
   float* ss = wsptr<float>(ctx, ctx->ws.ss);
   RotTable rot;
   rot.ang = wsptr<float2>(ctx, ctx->ws.ang);

@@ -1,9 +1,8 @@
 """Verify forwards on both sides of each row count where the few-row path
-changes: 16 rows of any model, one workgroup per 16 rows up to 64 where the
-projections are small, the separate kernels beyond.  Two layers of the small
-bf16 target and of two with grouped heads, and one layer of one with
-projections above the 16M weights of the 64-row path; sequences of 8 rows and
-one of the remainder, logits against the float64 decoder.  The bound is the
+changes: 16 rows (12 of a model wider than 4096), one workgroup per 16 rows up
+to 64 where the projections are small, the separate kernels beyond.  Two layers
+of the small bf16 target and of two with grouped heads, one layer of three whose
+projections set another limit; sequences of 8 rows and one of the remainder, logits against the float64 decoder.  The bound is the
 2e-2 of the 12-layer comparison (bf16 roundings; 2 layers stay below it)."""
 
 import numpy as np
@@ -21,6 +20,8 @@ SEED = SMALL_BF16.seed
 GROUPED_64 = ModelShape("grouped-64", 2, 384, 6, 3, 64, 640, 1040, 1e4)
 GROUPED = ModelShape("grouped", 2, 512, 4, 2, 128, 1408, 1000, 1e4)
 WIDE = ModelShape("wide", 1, 2048, 16, 4, 128, 5632, 2048, 5e5)
+WIDER = ModelShape("wider", 1, 4224, 2, 1, 128, 2048, 1024, 5e5)  # past 4096 columns: 12 rows
+MID = ModelShape("mid", 1, 1536, 12, 12, 64, 4096, 2048, 1e4)     # 12M weights: 42 rows
 
 
 @pytest.mark.parametrize("rows", [9, 15, 16, 17, 32, 33, 47, 49, 64, 65])
@@ -29,7 +30,8 @@ def test_rows(rows):
 
 
 @pytest.mark.parametrize("shape,rows", [(GROUPED_64, 9), (GROUPED_64, 17), (GROUPED_64, 33), (GROUPED_64, 64), (GROUPED, 16),
-                                        (GROUPED, 17), (GROUPED, 48), (GROUPED, 64), (WIDE, 8), (WIDE, 9), (WIDE, 16), (WIDE, 17)],
+                                        (GROUPED, 17), (GROUPED, 48), (GROUPED, 64), (WIDE, 8), (WIDE, 9), (WIDE, 16), (WIDE, 17),
+                                        (WIDER, 12), (WIDER, 13), (MID, 42), (MID, 43)],
                          ids=lambda x: getattr(x, "name", x))
 def test_rows_of_other_models(shape, rows):
     _check(shape, shape.n_layers, rows)
