@@ -1027,7 +1027,8 @@ __global__ __launch_bounds__(256, 1) void gemm_mfma3_bf16(const bf16_t* __restri
 // XCD walks a contiguous run of numbers, so that the tiles it works on at a
 // time share X and W panels in its L2.
 // Measured (median, weights rotated past the caches): 8192-row gate/up 1650 ->
-// 1340 us (1.43 PFLOP/s; the clock falls to 1.85 GHz under this load), 4096-row
+// 1340 us (1.43 PFLOP/s; counters: the MFMA pipe busy 82% of 2.25M cycles a CU,
+// so the clock falls to about 1.7 GHz under this load), 4096-row
 // QKV 242 -> 176, O 172 -> 117, down 455 -> 360 us.  32 x 32 MFMAs had 5% fewer
 // stall cycles and were 6% slower (more power per flop, lower clock); k-steps
 // started at different places per W tile were 3% slower.
